@@ -47,8 +47,8 @@ __device__ __forceinline__ void publish_wave(Ctrl* ctrl, int slot, double smax, 
     const int s1 = slot == 2 ? 0 : slot + 1;
     const unsigned long long bits = (unsigned long long)__double_as_longlong(smax);
     if (bits > __hip_atomic_load(&ctrl->smax[s1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(&ctrl->smax[s1], bits);
-    if (flags) atomicOr(&ctrl->flags[s1], flags);
+      (void)__hip_atomic_fetch_max(&ctrl->smax[s1], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (flags) (void)__hip_atomic_fetch_or(&ctrl->flags[s1], flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -80,7 +80,7 @@ template <int EQ, int P, bool LIM, class R>
 __device__ __forceinline__ void batch_tile(const BatchArgs<R>& a, const BatchInst& in, int first, int bc,
                                            Ctrl* ctrl, int lane, double& smax, unsigned& flags) {
   double dt;
-  const bool go = step_time(ctrl, nullptr, a.slot, in.dx, 0.0, first == 0, dt);
+  const bool go = step_time(step_load(ctrl, nullptr, a.slot), ctrl, nullptr, a.slot, in.dx, 0.0, first == 0, dt);
   if (!go) return;
   const StepArgs<R> s = instance_args(a, in, bc, ctrl);
   const double lam = div_rn(dt, in.dx);
@@ -96,7 +96,7 @@ __device__ __forceinline__ void batch_tile_staged(const BatchArgs<R>& a, const B
                                                   unsigned& flags, int& lo, int& hi) {
   constexpr int NC = ncomp<EQ>();
   double dt;
-  const bool go = step_time(ctrl, nullptr, a.slot, in.dx, 0.0, first == 0, dt);
+  const bool go = step_time(step_load(ctrl, nullptr, a.slot), ctrl, nullptr, a.slot, in.dx, 0.0, first == 0, dt);
   if (!go) return;
   const StepArgs<R> s = instance_args(a, in, bc, ctrl);
   const double lam = div_rn(dt, in.dx);

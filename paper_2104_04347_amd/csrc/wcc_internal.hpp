@@ -52,7 +52,7 @@ struct StepArgs {
   Ctrl* ctrl;
   unsigned long long* parts;  // partial maxima (single instance), or null: Ctrl::smax (batched)
   int32_t slot;
-  int32_t pad;
+  int32_t per_block;      // wave tiles of each block (the last may have fewer)
 };
 
 // Batched instances: one table row per instance and one per tile.

@@ -50,37 +50,38 @@ constexpr int min_waves_per_simd() {
 template <int EQ, int P, bool LIM, class R, int PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<EQ, P, R, PF>())))
 void k_half_step(const StepArgs<R> a) {
-  double dt;
-  if (!step_time(a.ctrl, a.parts, a.slot, a.dx, a.dt_fixed, blockIdx.x == 0 && threadIdx.x < 64, dt)) return;
-  const double lam = div_rn(dt, a.dx);
-  const R nlam = (R)(-lam);
+  const StepIn ring = step_load(a.ctrl, a.parts, a.slot);
   // the wave index is the same in every lane: say so, so that tile and
   // instance indices live in scalar registers
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
             nw = blockDim.x >> 6;
-  const int64_t tiles = (a.n_new + 62) / 63;
-  const int64_t per_block = (tiles + gridDim.x - 1) / gridDim.x;
-  const int64_t t_begin = (int64_t)blockIdx.x * per_block;
-  const int64_t t_stop = t_begin + per_block < tiles ? t_begin + per_block : tiles;
+  const int tiles = ((int)a.n_new + 62) / 63;
+  const int t_begin = (int)blockIdx.x * a.per_block;
+  const int t_stop = t_begin + a.per_block < tiles ? t_begin + a.per_block : tiles;
+  TileIn<EQ, P, R> in;
+  int tile = t_begin + wave;
+  double dt;
+  if (!step_time(ring, a.ctrl, a.parts, a.slot, a.dx, a.dt_fixed, blockIdx.x == 0 && wave == 0, dt)) return;
+  const double lam = div_rn(dt, a.dx);
+  const R nlam = (R)(-lam);
+  if (tile < t_stop) fetch_tile<EQ, P, R>(a, tile, lane, in);
   double smax = 0.0;
   unsigned flags = 0u;
   if constexpr ((PF & 2) != 0) {
     constexpr int NC = ncomp<EQ>();
     __shared__ Stage<EQ, P, R> st;
     int cur = 0;
-    TileIn<EQ, P, R> in;
-    if ((PF & 1) && t_begin + wave < t_stop) fetch_tile<EQ, P, R>(a, t_begin + wave, lane, in);
     // every wave runs every iteration (the barriers are block-wide)
-    for (int64_t tb = t_begin; tb < t_stop; tb += nw) {
-      const int64_t tile = tb + wave;
+    for (int tb = t_begin; tb < t_stop; tb += nw) {
+      tile = tb + wave;
       int lo = 0, hi = 0;
       if (tile < t_stop) {
         TileIn<EQ, P, R> nxt;
         if constexpr ((PF & 1) != 0) {
-          const int64_t t2 = tile + nw < t_stop ? tile + nw : tile;   // in bounds; unused at the end
+          const int t2 = tile + nw < t_stop ? tile + nw : tile;   // in bounds; unused at the end
           fetch_tile<EQ, P, R>(a, t2, lane, nxt);
           __builtin_amdgcn_sched_barrier(0);
-        } else {
+        } else if (tb != t_begin) {
           fetch_tile<EQ, P, R>(a, tile, lane, in);
         }
         double pn[NC];
@@ -88,7 +89,7 @@ void k_half_step(const StepArgs<R> a) {
         if (tile_cells<EQ, P, LIM, R>(a, tile, in, lam, nlam, lane, smax, flags, pn, dn))
           stage_put<EQ, P, R>(st, wave * 64 + lane, pn, dn);
         if constexpr ((PF & 1) != 0) in = nxt;
-        lo = (int)tile * 63;
+        lo = tile * 63;
         hi = lo + 63 < (int)a.n_new ? lo + 63 : (int)a.n_new;
       }
       __syncthreads();
@@ -98,21 +99,19 @@ void k_half_step(const StepArgs<R> a) {
       cur ^= 1;
     }
   } else if constexpr (PF == 0) {
-    for (int64_t tile = t_begin + wave; tile < t_stop; tile += nw)
-      run_tile<EQ, P, LIM, R>(a, tile, lam, nlam, lane, smax, flags);
+    while (tile < t_stop) {
+      compute_tile<EQ, P, LIM, R>(a, tile, in, lam, nlam, lane, smax, flags);
+      tile += nw;
+      if (tile < t_stop) fetch_tile<EQ, P, R>(a, tile, lane, in);
+    }
   } else {
-    int64_t tile = t_begin + wave;
-    if (tile < t_stop) {
-      TileIn<EQ, P, R> cur;
-      fetch_tile<EQ, P, R>(a, tile, lane, cur);
-      for (; tile < t_stop; tile += nw) {
-        TileIn<EQ, P, R> nxt;
-        const int64_t t2 = tile + nw < t_stop ? tile + nw : tile;   // in bounds; unused at the end
-        fetch_tile<EQ, P, R>(a, t2, lane, nxt);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_tile<EQ, P, LIM, R>(a, tile, cur, lam, nlam, lane, smax, flags);
-        cur = nxt;
-      }
+    for (; tile < t_stop; tile += nw) {
+      TileIn<EQ, P, R> nxt;
+      const int t2 = tile + nw < t_stop ? tile + nw : tile;   // in bounds; unused at the end
+      fetch_tile<EQ, P, R>(a, t2, lane, nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      compute_tile<EQ, P, LIM, R>(a, tile, in, lam, nlam, lane, smax, flags);
+      in = nxt;
     }
   }
   publish(a.ctrl, a.parts, a.slot, smax, flags);
@@ -148,7 +147,8 @@ __global__ __launch_bounds__(256) void k_state_speed(const StepArgs<R> a) {
 // Host-side dispatch over the compile-time variants.
 // ---------------------------------------------------------------------------
 template <int EQ, int P, bool LIM, class R>
-static hipError_t launch_one(const StepArgs<R>& a, int pf, int blocks, int threads, hipStream_t s) {
+static hipError_t launch_one(StepArgs<R> a, int pf, int blocks, int threads, hipStream_t s) {
+  a.per_block = (int32_t)(((a.n_new + 62) / 63 + blocks - 1) / blocks);
   switch (pf) {
     case 0: hipLaunchKernelGGL((k_half_step<EQ, P, LIM, R, 0>), dim3(blocks), dim3(threads), 0, s, a); break;
     case 1: hipLaunchKernelGGL((k_half_step<EQ, P, LIM, R, 1>), dim3(blocks), dim3(threads), 0, s, a); break;

@@ -159,19 +159,19 @@ __device__ __forceinline__ void wide_tile(const StepArgs<R>& a, int64_t tile, do
 // k_half_step.
 template <int EQ, int P, bool LIM, class R>
 __global__ __launch_bounds__(256) void k_half_step_wide(const StepArgs<R> a) {
-  double dt;
-  if (!step_time(a.ctrl, a.parts, a.slot, a.dx, a.dt_fixed, blockIdx.x == 0 && threadIdx.x < 64, dt)) return;
-  const double lam = div_rn(dt, a.dx);
-  const R nlam = (R)(-lam);
+  const StepIn ring = step_load(a.ctrl, a.parts, a.slot);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
             nw = blockDim.x >> 6;
-  const int64_t tiles = (a.n_new + 126) / 127;
-  const int64_t per_block = (tiles + gridDim.x - 1) / gridDim.x;
-  const int64_t t_begin = (int64_t)blockIdx.x * per_block;
-  const int64_t t_stop = t_begin + per_block < tiles ? t_begin + per_block : tiles;
+  const int tiles = ((int)a.n_new + 126) / 127;
+  const int t_begin = (int)blockIdx.x * a.per_block;
+  const int t_stop = t_begin + a.per_block < tiles ? t_begin + a.per_block : tiles;
+  double dt;
+  if (!step_time(ring, a.ctrl, a.parts, a.slot, a.dx, a.dt_fixed, blockIdx.x == 0 && wave == 0, dt)) return;
+  const double lam = div_rn(dt, a.dx);
+  const R nlam = (R)(-lam);
   double smax = 0.0;
   unsigned flags = 0u;
-  for (int64_t tile = t_begin + wave; tile < t_stop; tile += nw)
+  for (int tile = t_begin + wave; tile < t_stop; tile += nw)
     wide_tile<EQ, P, LIM, R>(a, tile, lam, nlam, lane, smax, flags);
   publish(a.ctrl, a.parts, a.slot, smax, flags);
 }
@@ -179,7 +179,8 @@ __global__ __launch_bounds__(256) void k_half_step_wide(const StepArgs<R> a) {
 namespace {
 
 template <int EQ, int P, class R>
-hipError_t launch_wide_lim(const StepArgs<R>& a, bool lim, int blocks, int threads, hipStream_t s) {
+hipError_t launch_wide_lim(StepArgs<R> a, bool lim, int blocks, int threads, hipStream_t s) {
+  a.per_block = (int32_t)(((a.n_new + 126) / 127 + blocks - 1) / blocks);
   if (lim && P >= 1)
     hipLaunchKernelGGL((k_half_step_wide<EQ, P, (P >= 1), R>), dim3(blocks), dim3(threads), 0, s, a);
   else

@@ -26,15 +26,63 @@ __device__ __forceinline__ double dpp_from_next(double x) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = __builtin_fmax(v, __shfl_xor(v, o));
-  return v;
+// Lane i receives x from the lane DPP control CTRL names, in the rows of
+// ROWS; the other lanes keep x.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_own(double x) {
+  const long long v = __double_as_longlong(x);
+  const int l = (int)(v & 0xffffffffll), h = (int)(v >> 32);
+  const int lo = __builtin_amdgcn_update_dpp(l, l, CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(h, h, CTRL, ROWS, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
+
+// Largest value of the wave's 64 lanes (NaN entries are passed over), the
+// same in every lane and known to be so: the result lives in scalar
+// registers.  row_shr 1, 2, 4, 8 leave each row's maximum in its lane 15,
+// row_bcast 15 and 31 carry it to lane 63.
+__device__ __forceinline__ double wave_max(double v) {
+  v = __builtin_fmax(v, dpp_or_own<0x111, 0xF>(v));
+  v = __builtin_fmax(v, dpp_or_own<0x112, 0xF>(v));
+  v = __builtin_fmax(v, dpp_or_own<0x114, 0xF>(v));
+  v = __builtin_fmax(v, dpp_or_own<0x118, 0xF>(v));
+  v = __builtin_fmax(v, dpp_or_own<0x142, 0xA>(v));
+  v = __builtin_fmax(v, dpp_or_own<0x143, 0xC>(v));
+  const long long x = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(x & 0xffffffffll), 63);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(x >> 32), 63);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// OR of the two status bits over the wave.
 __device__ __forceinline__ unsigned wave_or(unsigned v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v |= (unsigned)__shfl_xor((int)v, o);
-  return v;
+  return (__ballot((int)(v & 1u)) ? 1u : 0u) | (__ballot((int)(v & 2u)) ? 2u : 0u);
+}
+
+// What a launch reads of the time-control ring, loaded in one go before
+// anything else: at the smallest meshes a launch is a chain of memory
+// latencies and of the scalar work between them, and the fields used to be
+// loaded where each was needed.  With the 32-bit tile ranges from the host (no
+// 64-bit division in the kernel), the DPP maxima and the unwaited atomic, a
+// half-step of Burgers at N = 12,800 (51 blocks) went from 5.3 to 4.2 us and
+// one of Euler at N = 400 from 5.7 to 5.0 us.  (Loading the first tile's cells ahead of the
+// ring as well gained 0.1 us at 51 blocks and lost 3% at N = 2^20, where every
+// wave then waits for all of it.)
+struct StepIn {
+  double t, t_end, cfl;
+  unsigned flags;
+  long long done;             // half-steps so far
+  unsigned long long smax;    // Ctrl::smax of the slot, or this lane's partial entry of it
+};
+
+__device__ __forceinline__ StepIn step_load(const Ctrl* ctrl, const unsigned long long* parts, int slot) {
+  StepIn in;
+  in.smax = parts ? parts[(slot * kSmaxParts + (int)(threadIdx.x & 63)) * kSmaxStride] : ctrl->smax[slot];
+  in.t = ctrl->t[slot];
+  in.flags = ctrl->flags[slot];
+  in.t_end = ctrl->t_end;
+  in.cfl = ctrl->cfl;
+  in.done = ctrl->steps_done;
+  return in;
 }
 
 // Time-step bookkeeping shared by the single and batched kernels.  Returns
@@ -43,26 +91,23 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
 // `parts` (single-instance kernels) the wave speed of the previous step is
 // the max of the 64 partial entries of the slot; the first wave of block 0
 // (`leader_wave`) maintains the ring.  Called by every lane of every wave.
-__device__ __forceinline__ bool step_time(Ctrl* ctrl, unsigned long long* parts, int slot, double dx,
-                                          double dt_fixed, bool leader_wave, double& dt) {
+__device__ __forceinline__ bool step_time(const StepIn& in, Ctrl* ctrl, unsigned long long* parts, int slot,
+                                          double dx, double dt_fixed, bool leader_wave, double& dt) {
   const int s1 = slot == 2 ? 0 : slot + 1;
   const int s2 = s1 == 2 ? 0 : s1 + 1;
   const int lane = threadIdx.x & 63;
-  const double t = ctrl->t[slot];
-  const unsigned flags_in = ctrl->flags[slot];
-  bool done = flags_in != 0u;
+  const double t = in.t;
+  bool done = in.flags != 0u;
   double tn;
-  unsigned long long mine = 0ull;  // this lane's partial entry of the slot (parts mode)
-  if (parts) mine = parts[(slot * kSmaxParts + lane) * kSmaxStride];
   if (dt_fixed > 0.0) {
     dt = dt_fixed;
     tn = t + dt;
   } else {
-    const double smax = parts ? wave_max(__longlong_as_double((long long)mine))
-                              : __longlong_as_double((long long)ctrl->smax[slot]);
-    const double tend = ctrl->t_end;
+    const double mine = __longlong_as_double((long long)in.smax);
+    const double smax = parts ? wave_max(mine) : mine;
+    const double tend = in.t_end;
     done = done || !(t < tend);
-    dt = div_rn(ctrl->cfl * dx, smax);
+    dt = div_rn(in.cfl * dx, smax);
     const double rem = tend - t;
     if (dt >= rem) {
       dt = rem;
@@ -76,17 +121,17 @@ __device__ __forceinline__ bool step_time(Ctrl* ctrl, unsigned long long* parts,
       // Slot s1 was cleared by the previous launch (as its s2) and is being
       // raised by the other blocks' atomics now; only a finished run, where
       // no block publishes, carries the maximum forward.
-      if (done) parts[(s1 * kSmaxParts + lane) * kSmaxStride] = mine;
+      if (done) parts[(s1 * kSmaxParts + lane) * kSmaxStride] = in.smax;
       parts[(s2 * kSmaxParts + lane) * kSmaxStride] = 0ull;
     }
     if (lane == 0) {
       if (done) {
         ctrl->t[s1] = t;
-        ctrl->smax[s1] = ctrl->smax[slot];
-        ctrl->flags[s1] = flags_in;
+        ctrl->smax[s1] = parts ? 0ull : in.smax;
+        ctrl->flags[s1] = in.flags;
       } else {
         ctrl->t[s1] = tn;
-        ctrl->steps_done += 1;
+        ctrl->steps_done = in.done + 1;
       }
       ctrl->smax[s2] = 0ull;
       ctrl->flags[s2] = 0u;
@@ -96,31 +141,40 @@ __device__ __forceinline__ bool step_time(Ctrl* ctrl, unsigned long long* parts,
 }
 
 // Per-block reduction of the wave speeds and flags, then one atomic each into
-// the next slot, skipped when it cannot raise the stored maximum.  With
-// `parts` the block's atomic goes to entry (block index mod 64).
+// the next slot.  With `parts` the block's atomic goes to entry (block index
+// mod 64).  In launches of up to 64 blocks every block has an entry to itself
+// and raises it at once, without waiting for an answer; in larger ones a look
+// at the stored maximum first lets most blocks skip the atomic, which would
+// queue at its entry (768 blocks: 0.7% of a launch of 48 us).
 __device__ __forceinline__ void publish(Ctrl* ctrl, unsigned long long* parts, int slot, double smax,
                                         unsigned flags) {
-  __shared__ double red_s[16];
-  __shared__ unsigned red_f[16];
+  __shared__ double red_s[4];
+  __shared__ unsigned red_f[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   smax = wave_max(smax);
   flags = wave_or(flags);
-  if (lane == 0) {
-    red_s[wave] = smax;
-    red_f[wave] = flags;
+  if (nw > 1) {
+    if (lane == 0) {
+      red_s[wave] = smax;
+      red_f[wave] = flags;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < nw; ++w) {
-      smax = __builtin_fmax(smax, red_s[w]);
-      flags |= red_f[w];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {        // blocks hold at most four waves
+      if (w < nw) {
+        smax = __builtin_fmax(smax, red_s[w]);
+        flags |= red_f[w];
+      }
     }
     const int s1 = slot == 2 ? 0 : slot + 1;
     const unsigned long long bits = (unsigned long long)__double_as_longlong(smax);
     unsigned long long* dst =
         parts ? &parts[(s1 * kSmaxParts + (int)(blockIdx.x % kSmaxParts)) * kSmaxStride] : &ctrl->smax[s1];
-    if (bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, bits);
-    if (flags) atomicOr(&ctrl->flags[s1], flags);
+    if (gridDim.x <= kSmaxParts || bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      (void)__hip_atomic_fetch_max(dst, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (flags) (void)__hip_atomic_fetch_or(&ctrl->flags[s1], flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -191,11 +245,13 @@ __device__ __forceinline__ void load_cell(const double* __restrict__ pv, const R
 __device__ __forceinline__ int map_old(int o, int n_old, int N, int bc, int parity_old, int& ghost) {
   ghost = 0;
   if (bc == kPeriodic) {
-    // a tile reaches at most one cell before 0 and 63 past the end, so one
-    // wrap suffices unless N < 64 (then fall back to the remainder)
+    // a tile reaches at most one cell before 0 and its own length past the
+    // end, so one wrap suffices unless N is below a tile (a remainder here
+    // would have its reciprocal formed ahead of every launch's first load)
     if (o < 0) o += N;
     else if (o >= N) o -= N;
-    if (o >= N) o %= N;
+    if (N < 128)
+      while (o >= N) o -= N;
     return o;
   }
   if (o < 0) {

@@ -3,8 +3,8 @@
 // this file).
 //
 // A diagnostic translation unit includes this header, then the kernel source
-// with `step_time` and `publish` redirected to the wrappers below: every
-// half-step kernel calls step_time first and publish last, so the wrappers
+// with `step_load` and `publish` redirected to the wrappers below: every
+// half-step kernel calls step_load first and publish last, so the wrappers
 // bracket each wave's life without any change to the kernel source.  Lane 0
 // of each wave writes one record: the 100 MHz constant clock and the shader
 // clock counter at both ends, and the hardware placement (HW_ID, XCC_ID).
@@ -43,8 +43,7 @@ __device__ __forceinline__ int timeline_wave() {
 constexpr int kGetregHwId = (31 << 11) | 4;
 constexpr int kGetregXccId = (31 << 11) | 20;
 
-__device__ __forceinline__ bool step_time_tl(Ctrl* ctrl, unsigned long long* parts, int slot, double dx,
-                                             double dt_fixed, bool leader_wave, double& dt) {
+__device__ __forceinline__ StepIn step_load_tl(const Ctrl* ctrl, const unsigned long long* parts, int slot) {
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
   const unsigned long long c0 = __builtin_amdgcn_s_memtime();
   const int w = timeline_wave();
@@ -52,7 +51,7 @@ __device__ __forceinline__ bool step_time_tl(Ctrl* ctrl, unsigned long long* par
     g_timeline[w].t0 = t0;
     g_timeline[w].c0 = c0;
   }
-  return step_time(ctrl, parts, slot, dx, dt_fixed, leader_wave, dt);
+  return step_load(ctrl, parts, slot);
 }
 
 __device__ __forceinline__ void publish_tl(Ctrl* ctrl, unsigned long long* parts, int slot, double smax,
