@@ -69,17 +69,19 @@ __device__ __forceinline__ double fmaT(double a, double b, double c) { return __
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double absT(double a) { return __builtin_fabs(a); }
 __device__ __forceinline__ float absT(float a) { return __builtin_fabsf(a); }
-__device__ __forceinline__ double sqrtT(double a) { return sqrt_rn(a); }
+__device__ __forceinline__ double sqrtT(double a) { return sqrt_rn_any(a); }
 __device__ __forceinline__ float sqrtT(float a) { return __builtin_amdgcn_sqrtf(a); }
 __device__ __forceinline__ bool finiteT(double a) { return __builtin_isfinite(a); }
 
 // Division in the bulk type.  binary64: the correctly rounded quotient
-// (div_rn; the binary64 mode is bit-reproducible).  binary32 (FP32-mixed mode, checked against the FP64
+// (div_rn_any; the binary64 mode is bit-reproducible).  Functions with a NEAR
+// parameter replace it by the shorter forms of wcc_rn.hpp (binary64 only) and
+// clear `ok` in lanes whose operands are out of their ranges.  binary32 (FP32-mixed mode, checked against the FP64
 // oracle with a tolerance): the hardware reciprocal (1 ulp) times the
 // numerator, both scaled by 2^100 when the divisor is below 2^-100 so that
 // subnormal divisors (the limiter's epsilon is a binary32 subnormal) do not
 // overflow the reciprocal; the scaling by a power of two is exact.
-__device__ __forceinline__ double divT(double a, double b) { return div_rn(a, b); }
+__device__ __forceinline__ double divT(double a, double b) { return div_rn_any(a, b); }
 __device__ __forceinline__ float divT(float a, float b) {
   const bool tiny = __builtin_fabsf(b) < 0x1p-100f;
   const float s = tiny ? 0x1p100f : 1.0f;
@@ -153,9 +155,9 @@ struct OldOut {
 //   d[c][k] : scaled derivatives, k = 1..P (bulk type)
 //   nlam    : -dt/dx in the bulk type
 // ---------------------------------------------------------------------------
-template <int EQ, int P, class R>
+template <int EQ, int P, bool NEAR = false, class R>
 __device__ __forceinline__ void old_cell(const double (&p)[ncomp<EQ>()], const R (&d)[ncomp<EQ>()][P + 1],
-                                         R nlam, const Phys<R>& ph, OldOut<EQ, P, R>& out) {
+                                         R nlam, const Phys<R>& ph, OldOut<EQ, P, R>& out, bool& ok) {
   constexpr int NC = ncomp<EQ>();
   Tri<R, P> T[NC];   // u
   Tri<R, P> G[NC];   // f(u)
@@ -182,7 +184,14 @@ __device__ __forceinline__ void old_cell(const double (&p)[ncomp<EQ>()], const R
       } else if constexpr (EQ == kBurgers) {
         G[0].v[k][j] = (R)0.5 * tri_mul<P>(T[0], T[0], k, j);
       } else {
-        if (k == 0 && j == 0) rinv = divT((R)1.0, T[0].v[0][0]);
+        if (k == 0 && j == 0) {
+          if constexpr (NEAR) {
+            rinv = rcp_near(T[0].v[0][0]);
+            ok &= near_rcp(T[0].v[0][0]);
+          } else {
+            rinv = divT((R)1.0, T[0].v[0][0]);
+          }
+        }
         vel.v[k][j] = tri_div<P>(T[1], T[0], vel, rinv, k, j);
         const R kin = tri_mul<P>(T[1], vel, k, j);                     // rho u^2
         const R pre = ph.gm1 * (T[2].v[k][j] - (R)0.5 * kin);           // p
@@ -260,32 +269,59 @@ __device__ __forceinline__ R smoothness(const R (&d)[P + 1]) {
 //   binary32: the same weights after dividing every unnormalised weight by
 //             the largest one, so that the tiny epsilon (a binary32 subnormal)
 //             and ratios up to 1e80 neither overflow nor give inf/inf.
-template <int P>
+template <int P, bool NEAR>
 __device__ __forceinline__ void limiter_weights(double b0, double b1, double b2, double st, double eps,
-                                                double& w0, double& w1, double& w2) {
-  double wh0, wh1, wh2;
-  if (P == 1) {
-    const double q0 = div_rn(1.0, b0 + eps), q1 = div_rn(1.0, b1 + eps), q2 = div_rn(1.0, b2 + eps);
-    wh0 = q0 * q0;
-    wh1 = q1 * q1;
-    wh2 = q2 * q2;
+                                                double& w0, double& w1, double& w2, bool& ok) {
+  const double q0 = P == 1 ? b0 + eps : __builtin_fma(b0, b0, eps);
+  const double q1 = P == 1 ? b1 + eps : __builtin_fma(b1, b1, eps);
+  const double q2 = P == 1 ? b2 + eps : __builtin_fma(b2, b2, eps);
+  double r0, r1, r2;       // st / q_m (P = 1: 1 / q_m)
+  if constexpr (NEAR) {
+    r0 = rcp_near(q0);
+    r1 = rcp_near(q1);
+    r2 = rcp_near(q2);
+    if (P > 1) {
+      r0 = div_near(st, q0, r0);
+      r1 = div_near(st, q1, r1);
+      r2 = div_near(st, q2, r2);
+    }
   } else {
-    const double r0 = div_rn(st, __builtin_fma(b0, b0, eps));
-    const double r1 = div_rn(st, __builtin_fma(b1, b1, eps));
-    const double r2 = div_rn(st, __builtin_fma(b2, b2, eps));
-    wh0 = __builtin_fma(r0, r0, 1.0);
-    wh1 = r1 * r1;
-    wh2 = r2 * r2;
+    const double n = P == 1 ? 1.0 : st;
+    r0 = div_rn_any(n, q0);
+    r1 = div_rn_any(n, q1);
+    r2 = div_rn_any(n, q2);
   }
-  const double inv = div_rn(1.0, (wh0 + wh1) + wh2);
+  const double wh0 = P == 1 ? r0 * r0 : __builtin_fma(r0, r0, 1.0);
+  const double wh1 = r1 * r1, wh2 = r2 * r2;
+  const double sum = (wh0 + wh1) + wh2;
+  double inv;
+  if constexpr (NEAR) {
+    inv = rcp_near(sum);
+    // The four denominators' ranges.  q_m >= eps >= 2^-900 (near_eps, and
+    // b_m^2 >= 0), so only their upper bound is open, and a NaN's high word
+    // lies above it; sum >= 1 (P = 1: >= 2^-120).  Their low words are
+    // compared together.
+    const uint32_t qh = max(max(hi_word(q0), hi_word(q1)), hi_word(q2));
+    const uint32_t lo = max(max(max(lo_word(q0), lo_word(q1)), lo_word(q2)), lo_word(sum));
+    ok &= (qh < hi_pow2(P == 1 ? 900 : 60)) & (hi_word(sum) < hi_pow2(900)) & (lo != 0xffffffffu);
+    if (P > 1) ok &= near_num(st);
+    if (P == 1) ok &= hi_word(sum) >= hi_pow2(-900);
+  } else {
+    inv = div_rn_any(1.0, sum);
+  }
   w0 = wh0 * inv;
   w1 = wh1 * inv;
   w2 = wh2 * inv;
 }
 
-template <int P>
+// The limiter epsilon allows the near forms at all (a property of the run).
+__device__ __forceinline__ bool near_eps(double eps) {
+  return between_pow2(eps, -900, 0);
+}
+
+template <int P, bool NEAR>
 __device__ __forceinline__ void limiter_weights(float b0, float b1, float b2, float st, float eps,
-                                                float& w0, float& w1, float& w2) {
+                                                float& w0, float& w1, float& w2, bool&) {
   float wh0, wh1, wh2;
   if (P == 1) {
     // w_m = (1/q_m)^2 / sum_l (1/q_l)^2 = (qmin/q_m)^2 / sum_l (qmin/q_l)^2
@@ -323,8 +359,8 @@ __device__ __forceinline__ void limiter_weights(float b0, float b1, float b2, fl
 // (Section 2.2): candidates of Eq. 1D_U012 built from the average abar and the
 // vertex values vl, vr; the limited polynomial keeps abar and replaces
 // d1 <- w0 d1 + w1 s1 + w2 s2, dk <- w0 dk.
-template <int P, class R>
-__device__ __forceinline__ void limit_field(R (&d)[P + 1], R abar, R vl, R vr, R eps) {
+template <int P, bool NEAR, class R>
+__device__ __forceinline__ void limit_field(R (&d)[P + 1], R abar, R vl, R vr, R eps, bool& ok) {
   const R s1 = (abar - vl) * (R)2.0;
   const R s2 = (vr - abar) * (R)2.0;
   R b0, st = (R)0;
@@ -348,7 +384,7 @@ __device__ __forceinline__ void limit_field(R (&d)[P + 1], R abar, R vl, R vr, R
   }
   const R b1 = s1 * s1, b2 = s2 * s2;
   R w0, w1, w2;
-  limiter_weights<P>(b0, b1, b2, st, eps, w0, w1, w2);
+  limiter_weights<P, NEAR>(b0, b1, b2, st, eps, w0, w1, w2, ok);
   R d1 = w0 * d[1];
   d1 = fmaT(w1, s1, d1);
   d1 = fmaT(w2, s2, d1);
@@ -357,12 +393,36 @@ __device__ __forceinline__ void limit_field(R (&d)[P + 1], R abar, R vl, R vr, R
   for (int k = 2; k <= P; ++k) d[k] = w0 * d[k];
 }
 
-// Velocity, pressure and sound speed of a conserved Euler state.
-template <class R>
-__device__ __forceinline__ void euler_uc(const Phys<R>& ph, R rho, R mom, R ene, R& u, R& p, R& c) {
-  u = divT(mom, rho);
-  p = ph.gm1 * (ene - (R)0.5 * mom * u);
-  c = sqrtT(divT(ph.gamma * p, rho));
+// Velocity, pressure and sound speed of a conserved Euler state; with CHAR also
+// the total enthalpy H and 1 / c of the characteristic decomposition.
+template <bool CHAR, bool NEAR = false, class R>
+__device__ __forceinline__ void euler_uc(const Phys<R>& ph, R rho, R mom, R ene, R& u, R& p, R& c, R& H, R& ic,
+                                         bool& ok) {
+  if constexpr (NEAR) {
+    // the quotients by rho share its reciprocal
+    const double y = rcp_near(rho);
+    u = div_near(mom, rho, y);
+    p = ph.gm1 * (ene - 0.5 * mom * u);
+    const double gp = ph.gamma * p;
+    c = sqrt_near(div_near(gp, rho, y));
+    // the ranges of rho and gamma p put c^2 in [2^-460, 2^400], inside those
+    // of the square root and, up to its low word, of 1 / c
+    ok &= between_pow2(rho, -300, 60) & not_ones(rho) & near_num(mom) & between_pow2(gp, -400, 100);
+    if (CHAR) {
+      const double h = ene + p;
+      H = div_near(h, rho, y);
+      ic = rcp_near(c);
+      ok &= between_pow2(h, -400, 100) & not_ones(c);
+    }
+  } else {
+    u = divT(mom, rho);
+    p = ph.gm1 * (ene - (R)0.5 * mom * u);
+    c = sqrtT(divT(ph.gamma * p, rho));
+    if (CHAR) {
+      H = divT(ene + p, rho);
+      ic = divT((R)1.0, c);
+    }
+  }
 }
 
 template <class R>
@@ -378,11 +438,11 @@ __device__ __forceinline__ void mat3_apply(const R (&M)[3][3], R x0, R x1, R x2,
 // Writes the new point values pn[c], derivatives dn[c][1..P], the wave speed
 // and the status bits (1: non-finite, 2: rho <= 0 or p <= 0).
 // ---------------------------------------------------------------------------
-template <int EQ, int P, bool LIM, class R>
+template <int EQ, int P, bool LIM, bool NEAR = false, class R>
 __device__ __forceinline__ int new_cell(const OldOut<EQ, P, R>& L, const double (&uL_R)[ncomp<EQ>()],
                                         const R (&fbar_R)[ncomp<EQ>()], const R (&V_R)[ncomp<EQ>()][P > 0 ? P : 1],
                                         double lam, const Phys<R>& ph, double (&pn)[ncomp<EQ>()],
-                                        R (&dn)[ncomp<EQ>()][P + 1], double& speed) {
+                                        R (&dn)[ncomp<EQ>()][P + 1], double& speed, bool& ok) {
   constexpr int NC = ncomp<EQ>();
   double abar[NC];
 #pragma unroll
@@ -399,9 +459,9 @@ __device__ __forceinline__ int new_cell(const OldOut<EQ, P, R>& L, const double 
     }
   }
   int flag = 0;
-  R eu = (R)0, ep = (R)0, ec = (R)0;
+  R eu = (R)0, ep = (R)0, ec = (R)0, H = (R)0, ic = (R)0;
   if constexpr (EQ == kEuler) {
-    euler_uc(ph, (R)abar[0], (R)abar[1], (R)abar[2], eu, ep, ec);
+    euler_uc<LIM && P >= 1, NEAR>(ph, (R)abar[0], (R)abar[1], (R)abar[2], eu, ep, ec, H, ic, ok);
     speed = (double)(absT(eu) + ec);
     if (!(abar[0] > 0.0) || !(ep > (R)0)) flag |= 2;
   } else if constexpr (EQ == kBurgers) {
@@ -415,7 +475,7 @@ __device__ __forceinline__ int new_cell(const OldOut<EQ, P, R>& L, const double 
       R df[P + 1];
 #pragma unroll
       for (int k = 0; k <= P; ++k) df[k] = dn[0][k];
-      limit_field<P>(df, (R)abar[0], L.V[0][0], V_R[0][0], ph.eps);
+      limit_field<P, NEAR>(df, (R)abar[0], L.V[0][0], V_R[0][0], ph.eps, ok);
 #pragma unroll
       for (int k = 1; k <= P; ++k) dn[0][k] = df[k];
     } else {
@@ -423,9 +483,6 @@ __device__ __forceinline__ int new_cell(const OldOut<EQ, P, R>& L, const double 
       // one characteristic field at a time: row f of L projects the average,
       // the two vertex values and the derivatives; the limited field is added
       // into R*cd column by column (the same order as a full 3x3 product).
-      const R rho = (R)abar[0];
-      const R H = divT((R)abar[2] + ep, rho);
-      const R ic = divT((R)1.0, ec);
       const R b1 = ph.gm1 * (ic * ic);
       const R b2 = (R)0.5 * b1 * (eu * eu);
       const R uic = eu * ic, b1u = b1 * eu;
@@ -454,7 +511,7 @@ __device__ __forceinline__ int new_cell(const OldOut<EQ, P, R>& L, const double 
         for (int k = 1; k <= P; ++k) {
           s = l0 * dn[0][k]; s = fmaT(l1, dn[1][k], s); cd[k] = fmaT(l2, dn[2][k], s);
         }
-        limit_field<P>(cd, ca, cl, cr, ph.eps);
+        limit_field<P, NEAR>(cd, ca, cl, cr, ph.eps, ok);
 #pragma unroll
         for (int k = 1; k <= P; ++k) {
           if (f == 0) {
@@ -485,10 +542,10 @@ __device__ __forceinline__ int new_cell(const OldOut<EQ, P, R>& L, const double 
 #pragma unroll
     for (int k = 2; k <= P; k += 2) pv = __builtin_fma(neg_avg(k), (double)dn[c][k], pv);
     pn[c] = pv;
-    bool ok = __builtin_isfinite(pv);
+    bool fin = __builtin_isfinite(pv);
 #pragma unroll
-    for (int k = 1; k <= P; ++k) ok = ok && finiteT(dn[c][k]);
-    if (!ok) flag |= 1;
+    for (int k = 1; k <= P; ++k) fin = fin && finiteT(dn[c][k]);
+    if (!fin) flag |= 1;
   }
   if (!__builtin_isfinite(speed)) flag |= 1;
   return flag;
@@ -509,8 +566,9 @@ __device__ __forceinline__ double stored_speed(const double (&p)[ncomp<EQ>()], c
     abar[c] = s;
   }
   if constexpr (EQ == kEuler) {
-    R u, pr, c;
-    euler_uc(ph, (R)abar[0], (R)abar[1], (R)abar[2], u, pr, c);
+    R u, pr, c, H, ic;
+    bool ok = true;
+    euler_uc<false>(ph, (R)abar[0], (R)abar[1], (R)abar[2], u, pr, c, H, ic, ok);
     return (double)(absT(u) + c);
   } else if constexpr (EQ == kBurgers) {
     return __builtin_fabs(abar[0]);

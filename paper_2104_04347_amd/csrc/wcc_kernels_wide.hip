@@ -100,8 +100,9 @@ __device__ __forceinline__ void wide_tile(const StepArgs<R>& a, int64_t tile, do
   fetch_old<EQ, P, R>(a, j0 + lane - shift, inA);
   fetch_old<EQ, P, R>(a, j0 + 64 + lane - shift, inB);
   OldOut<EQ, P, R> XA, XB;
-  old_cell<EQ, P, R>(inA.p, inA.d, nlam, a.ph, XA);
-  old_cell<EQ, P, R>(inB.p, inB.d, nlam, a.ph, XB);
+  bool ok = true;
+  old_cell<EQ, P>(inA.p, inA.d, nlam, a.ph, XA, ok);
+  old_cell<EQ, P>(inB.p, inB.d, nlam, a.ph, XB, ok);
   __builtin_amdgcn_sched_barrier(0);
 
   // first half: right parents A_{l+1}, and B_0 for lane 63
@@ -121,7 +122,7 @@ __device__ __forceinline__ void wide_tile(const StepArgs<R>& a, int64_t tile, do
     if (j < (int)a.n_new) {
       double pn[NC], sp;
       R dn[NC][P + 1];
-      flags |= (unsigned)new_cell<EQ, P, LIM, R>(XA, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp);
+      flags |= (unsigned)new_cell<EQ, P, LIM>(XA, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp, ok);
       smax = __builtin_fmax(smax, sp);
       if (!(sp == sp)) smax = sp;
       store_new<EQ, P, R>(a, j, pn, dn);
@@ -144,7 +145,7 @@ __device__ __forceinline__ void wide_tile(const StepArgs<R>& a, int64_t tile, do
     if (lane < 63 && j < (int)a.n_new) {
       double pn[NC], sp;
       R dn[NC][P + 1];
-      flags |= (unsigned)new_cell<EQ, P, LIM, R>(XB, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp);
+      flags |= (unsigned)new_cell<EQ, P, LIM>(XB, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp, ok);
       smax = __builtin_fmax(smax, sp);
       if (!(sp == sp)) smax = sp;
       store_new<EQ, P, R>(a, j, pn, dn);

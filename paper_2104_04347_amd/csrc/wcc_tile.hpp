@@ -301,15 +301,17 @@ __device__ __forceinline__ void fetch_tile(const StepArgs<R>& a, int64_t tile, i
 }
 
 // The new cell of this lane (lanes 0..62, cell 63 tile + lane, if it exists):
-// returns whether there is one and leaves it in pn / dn.
-template <int EQ, int P, bool LIM, class R>
-__device__ __forceinline__ bool tile_cells(const StepArgs<R>& a, int64_t tile, const TileIn<EQ, P, R>& in,
-                                          double lam, R nlam, int lane, double& smax, unsigned& flags,
+// returns whether there is one and leaves it in pn / dn, its wave speed in sp
+// and its status bits in fl.  NEAR: with the near divisions (wcc_rn.hpp); ok
+// falls in lanes whose results do not count.
+template <int EQ, int P, bool LIM, bool NEAR, class R>
+__device__ __forceinline__ bool tile_form(const StepArgs<R>& a, int64_t tile, const TileIn<EQ, P, R>& in,
+                                          double lam, R nlam, int lane, double& sp, unsigned& fl, bool& ok,
                                           double (&pn)[ncomp<EQ>()], R (&dn)[ncomp<EQ>()][P + 1]) {
   constexpr int NC = ncomp<EQ>();
   constexpr int PV = P > 0 ? P : 1;
   OldOut<EQ, P, R> X;
-  old_cell<EQ, P, R>(in.p, in.d, nlam, a.ph, X);
+  old_cell<EQ, P, NEAR>(in.p, in.d, nlam, a.ph, X, ok);
   __builtin_amdgcn_sched_barrier(0);
 
   // Right parent's half of the interface data from lane + 1.
@@ -327,13 +329,48 @@ __device__ __forceinline__ bool tile_cells(const StepArgs<R>& a, int64_t tile, c
 
   const int j = (int)tile * 63 + lane;
   if (lane < 63 && j < (int)a.n_new) {
-    double sp;
-    flags |= (unsigned)new_cell<EQ, P, LIM, R>(X, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp);
-    smax = __builtin_fmax(smax, sp);
-    if (!(sp == sp)) smax = sp;
+    fl = (unsigned)new_cell<EQ, P, LIM, NEAR>(X, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp, ok);
     return true;
   }
   return false;
+}
+
+// One tile: the near form of its divisions, and where a lane's operands lie
+// outside their ranges (or the limiter's epsilon does, a property of the run)
+// the general form on the same inputs, read again so that they occupy no
+// registers until then.  One flag and one wave-uniform branch a tile, no
+// branches inside: at 17 divisions a cell (Euler, P = 3, limiter) a branch per
+// group of divisions cost 3% of the launch.
+template <int EQ, int P, bool LIM, class R>
+__device__ __forceinline__ bool tile_cells(const StepArgs<R>& a, int64_t tile, const TileIn<EQ, P, R>& in,
+                                          double lam, R nlam, int lane, double& smax, unsigned& flags,
+                                          double (&pn)[ncomp<EQ>()], R (&dn)[ncomp<EQ>()][P + 1]) {
+  constexpr bool divides = EQ == kEuler || (LIM && P >= 1);
+  constexpr bool near = sizeof(R) == 8 && divides;
+  double sp = 0.0;
+  unsigned fl = 0u;
+  bool mine = false, ok = true;
+  if constexpr (near) {
+    bool again = LIM && !near_eps(a.ph.eps);
+    if (!again) {
+      mine = tile_form<EQ, P, LIM, true>(a, tile, in, lam, nlam, lane, sp, fl, ok, pn, dn);
+      again = __ballot(!ok) != 0;
+    }
+    if (__builtin_expect(again, 0)) {
+      asm volatile("" ::: "memory");
+      TileIn<EQ, P, R> reread;
+      fetch_tile<EQ, P, R>(a, tile, lane, reread);
+      sp = 0.0;
+      fl = 0u;
+      mine = tile_form<EQ, P, LIM, false>(a, tile, reread, lam, nlam, lane, sp, fl, ok, pn, dn);
+    }
+  } else {
+    mine = tile_form<EQ, P, LIM, false>(a, tile, in, lam, nlam, lane, sp, fl, ok, pn, dn);
+  }
+  flags |= fl;
+  smax = __builtin_fmax(smax, sp);
+  if (!(sp == sp)) smax = sp;
+  return mine;
 }
 
 template <int EQ, int P, bool LIM, class R>
