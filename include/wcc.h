@@ -153,17 +153,19 @@ int wcc_write_dofs(wcc_ctx* ctx, const double* host, int64_t n_cells, int parity
  * dt_fixed), WCC_EDEVICE. */
 int wcc_step(wcc_ctx* ctx, double cfl, double dt_fixed);
 
-/* Enqueue `half_steps` CFL half-steps as wcc_step (no end time), replayed
- * from captured HIP graphs of a fixed number of kernels.  Stream-ordered;
- * the device time of the enqueued work is read with wcc_last_run_ms.
+/* Enqueue `half_steps` CFL half-steps as wcc_step (no end time): replayed
+ * from captured HIP graphs of a fixed number of kernels, or, for meshes of a
+ * few hundred cells in the default launch shape, up to 4,096 of them in one
+ * launch of one work-group.  Stream-ordered; the device time of the enqueued
+ * work is read with wcc_last_run_ms.
  * Errors as wcc_step. */
 int wcc_run(wcc_ctx* ctx, int64_t half_steps, double cfl);
 
 /* Advance to t_end with CFL time steps (Section 5 preamble; the step that
  * would pass t_end is clipped to it), at most max_half_steps (<= 0:
- * unlimited).  Synchronises at the end of every graph chunk to read the
- * 16-byte status.  *taken (may be NULL) receives the half-steps done by this
- * call.  Errors: WCC_ESTATE, WCC_EINVAL (t_end before the current time),
+ * unlimited).  Synchronises at the end of every chunk (a graph, or the one
+ * launch of a small mesh) to read the 16-byte status.  *taken (may be NULL)
+ * receives the half-steps done by this call.  Errors: WCC_ESTATE, WCC_EINVAL (t_end before the current time),
  * WCC_EDEVICE, WCC_ENONFINITE if a step raised a flag (the state after that
  * step is kept for inspection). */
 int wcc_advance(wcc_ctx* ctx, double t_end, double cfl, int64_t max_half_steps, int64_t* taken);

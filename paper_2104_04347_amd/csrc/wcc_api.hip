@@ -24,6 +24,7 @@
 #include "wcc.h"
 #include "wcc_internal.hpp"
 #include "wcc_ctrl.hpp"
+#include "wcc_march.hpp"
 #include "wcc_wide.hpp"
 
 using wcc::Ctrl;
@@ -64,6 +65,7 @@ struct wcc_ctx {
   int threads = 256, blocks = 0;
   int default_blocks = 0;    // device-filling grid of the current shape (0: not computed yet)
   int prefetch = 1;          // kernel variant bits: 1 = prefetch the next tile's inputs, 2 = aligned stores
+  int default_variant = 1;   // the variant chosen at creation
   int cu = 0;
   hipStream_t capture = nullptr;
   // captured chunks of kChunk half-steps from (slot, parity), key slot*2 + parity
@@ -219,6 +221,44 @@ int enqueue_step(wcc_ctx* c, int parity, int slot, double dt_fixed, hipStream_t 
   return enqueue_step_at(c, bound_lay(c), parity, slot, dt_fixed, s);
 }
 
+// Whether runs of half-steps go through the one-launch form (wcc_march.hip):
+// meshes of at most march_tiles tiles (where the line is and why: there) in
+// the default launch shape; a shape set by the caller is one of the
+// launch-per-half-step kernels.
+bool marches(const wcc_ctx* c) {
+  const int64_t tiles = (std::max(ncells_of(c, 0), ncells_of(c, 1)) + 62) / 63;
+  return tiles <= wcc::march_tiles(c->eq, c->P, (int)c->elem) && c->blocks == 0 && c->threads == 256 &&
+         c->prefetch == c->default_variant;
+}
+
+template <class R>
+hipError_t march_at(const wcc_ctx* c, const Lay& L, int parity, int slot, int steps, hipStream_t s) {
+  wcc::MarchArgs<R> a{};
+  for (int b = 0; b < 2; ++b) {
+    a.p[b] = L.p[b];
+    a.d[b] = static_cast<R*>(L.d[b]);
+  }
+  a.ld = (int32_t)c->ld;
+  a.N = (int32_t)c->N;
+  a.bc = c->bc;
+  a.parity = parity;
+  a.slot = slot;
+  a.steps = steps;
+  a.dx = dx_of(c);
+  a.ph = phys_of<R>(c);
+  a.ctrl = L.ctrl;
+  a.parts = L.parts;
+  return wcc::launch_march<R>(a, c->eq, c->P, c->prm.limiter != 0, s);
+}
+
+// Enqueue `steps` (1..kMarchSteps) half-steps as one launch.
+int enqueue_march(wcc_ctx* c, const Lay& L, int parity, int slot, int steps, hipStream_t s) {
+  const hipError_t e = c->prm.precision == WCC_FP64 ? march_at<double>(c, L, parity, slot, steps, s)
+                                                    : march_at<float>(c, L, parity, slot, steps, s);
+  if (e != hipSuccess) return fail(c, WCC_EDEVICE, "march launch: %s", hipGetErrorString(e));
+  return WCC_OK;
+}
+
 int current_parity(const wcc_ctx* c) { return (int)((c->parity_w + c->steps) & 1); }
 
 void drop_graphs(wcc_ctx* c) {
@@ -372,9 +412,12 @@ int wcc_run_noalloc(wcc_ctx* c, void* state, size_t bytes, int parity, double t,
     e = wcc::launch_state_speed<float>(a, c->eq, c->P, blocks, s);
   }
   if (e != hipSuccess) return fail(c, WCC_EDEVICE, "speed kernel: %s", hipGetErrorString(e));
-  for (int64_t i = 0; i < half_steps; ++i) {
-    rc = enqueue_step_at(c, L, (int)((parity + i) & 1), (int)(i % 3), 0.0, s);
+  for (int64_t i = 0; i < half_steps;) {
+    const int par = (int)((parity + i) & 1), slot = (int)(i % 3);
+    const int64_t n = marches(c) ? std::min<int64_t>(half_steps - i, wcc::kMarchSteps) : 1;
+    rc = n > 1 ? enqueue_march(c, L, par, slot, (int)n, s) : enqueue_step_at(c, L, par, slot, 0.0, s);
     if (rc) return rc;
+    i += n;
   }
   if (t_out) {
     Ctrl h;
@@ -428,7 +471,7 @@ int wcc_create(int equation, int P, int64_t N, int bc, const wcc_params* params,
   // Cache by about a factor two, the staged stores with prefetch are fastest
   // (the crossover lies between 0.50 and 0.60 GB); below, prefetch alone.
   const double state_bytes = 2.0 * (double)c->nc * (double)c->ld * (8.0 + (double)(c->P * c->elem));
-  c->prefetch = state_bytes > 512.0 * 1048576.0 ? 3 : 1;
+  c->prefetch = c->default_variant = state_bytes > 512.0 * 1048576.0 ? 3 : 1;
   int dev = 0;
   if (hipGetDevice(&dev) == hipSuccess) {
     hipDeviceProp_t prop;
@@ -573,7 +616,8 @@ static int run_chunks(wcc_ctx* c, int64_t n, bool timed) {
   // starts, which a short run cannot hide behind earlier work (measured:
   // a 20-half-step run took ~5 us per half-step more as one graph than as 20
   // launches).
-  if (n >= kChunk) {
+  const bool march = marches(c);
+  if (n >= kChunk && !march) {
     for (int key = 0; key < 6; ++key) {
       hipGraphExec_t g;
       const int rc = chunk_graph(c, key / 2, key % 2, &g);
@@ -588,7 +632,14 @@ static int run_chunks(wcc_ctx* c, int64_t n, bool timed) {
   int64_t left = n;
   while (left > 0) {
     const int slot = (int)(c->launched % 3), par = current_parity(c);
-    if (left >= kChunk) {
+    if (march && left > 1) {
+      const int64_t k = std::min<int64_t>(left, wcc::kMarchSteps);
+      int rc = enqueue_march(c, bound_lay(c), par, slot, (int)k, c->stream);
+      if (rc) return rc;
+      c->launched += k;
+      c->steps += k;
+      left -= k;
+    } else if (left >= kChunk) {
       hipGraphExec_t g;
       int rc = chunk_graph(c, slot, par, &g);
       if (rc) return rc;
@@ -648,8 +699,7 @@ int wcc_advance(wcc_ctx* c, double t_end, double cfl, int64_t max_half_steps, in
   while (true) {
     const int64_t done = c->steps - start;
     if (done >= cap) break;
-    const int64_t want = std::min<int64_t>(cap - done, kChunk);
-    rc = run_chunks(c, want >= kChunk ? kChunk : want, false);
+    rc = run_chunks(c, std::min<int64_t>(cap - done, marches(c) ? wcc::kMarchSteps : kChunk), false);
     if (rc) return rc;
     rc = read_ctrl(c, &h);  // sets c->steps from the device
     if (rc) return rc;

@@ -105,7 +105,8 @@ __device__ __forceinline__ void batch_tile_staged(const BatchArgs<R>& a, const B
   fetch_tile<EQ, P, R>(s, first, lane, ti);
   double pn[NC];
   R dn[NC][P + 1];
-  if (tile_cells<EQ, P, LIM, R>(s, first, ti, lam, (R)(-lam), lane, smax, flags, pn, dn))
+  auto reread = [&](TileIn<EQ, P, R>& x) { fetch_tile<EQ, P, R>(s, first, lane, x); };
+  if (tile_cells<EQ, P, LIM, R>(s.ph, (int)s.n_new, first, ti, reread, lam, (R)(-lam), lane, smax, flags, pn, dn))
     stage_put<EQ, P, R>(st, wave * 64 + lane, pn, dn);
   lo = first * 63;
   hi = lo + 63 < (int)s.n_new ? lo + 63 : (int)s.n_new;

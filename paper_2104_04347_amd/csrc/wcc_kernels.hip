@@ -86,7 +86,8 @@ void k_half_step(const StepArgs<R> a) {
         }
         double pn[NC];
         R dn[NC][P + 1];
-        if (tile_cells<EQ, P, LIM, R>(a, tile, in, lam, nlam, lane, smax, flags, pn, dn))
+        auto reread = [&](TileIn<EQ, P, R>& x) { fetch_tile<EQ, P, R>(a, tile, lane, x); };
+        if (tile_cells<EQ, P, LIM, R>(a.ph, (int)a.n_new, tile, in, reread, lam, nlam, lane, smax, flags, pn, dn))
           stage_put<EQ, P, R>(st, wave * 64 + lane, pn, dn);
         if constexpr ((PF & 1) != 0) in = nxt;
         lo = tile * 63;

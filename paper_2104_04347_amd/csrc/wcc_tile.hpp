@@ -305,13 +305,13 @@ __device__ __forceinline__ void fetch_tile(const StepArgs<R>& a, int64_t tile, i
 // and its status bits in fl.  NEAR: with the near divisions (wcc_rn.hpp); ok
 // falls in lanes whose results do not count.
 template <int EQ, int P, bool LIM, bool NEAR, class R>
-__device__ __forceinline__ bool tile_form(const StepArgs<R>& a, int64_t tile, const TileIn<EQ, P, R>& in,
+__device__ __forceinline__ bool tile_form(const Phys<R>& ph, int n_new, int tile, const TileIn<EQ, P, R>& in,
                                           double lam, R nlam, int lane, double& sp, unsigned& fl, bool& ok,
                                           double (&pn)[ncomp<EQ>()], R (&dn)[ncomp<EQ>()][P + 1]) {
   constexpr int NC = ncomp<EQ>();
   constexpr int PV = P > 0 ? P : 1;
   OldOut<EQ, P, R> X;
-  old_cell<EQ, P, NEAR>(in.p, in.d, nlam, a.ph, X, ok);
+  old_cell<EQ, P, NEAR>(in.p, in.d, nlam, ph, X, ok);
   __builtin_amdgcn_sched_barrier(0);
 
   // Right parent's half of the interface data from lane + 1.
@@ -327,9 +327,9 @@ __device__ __forceinline__ bool tile_form(const StepArgs<R>& a, int64_t tile, co
     if (P == 0) V_R[c][0] = (R)0;
   }
 
-  const int j = (int)tile * 63 + lane;
-  if (lane < 63 && j < (int)a.n_new) {
-    fl = (unsigned)new_cell<EQ, P, LIM, NEAR>(X, uL_R, fbar_R, V_R, lam, a.ph, pn, dn, sp, ok);
+  const int j = tile * 63 + lane;
+  if (lane < 63 && j < n_new) {
+    fl = (unsigned)new_cell<EQ, P, LIM, NEAR>(X, uL_R, fbar_R, V_R, lam, ph, pn, dn, sp, ok);
     return true;
   }
   return false;
@@ -341,9 +341,10 @@ __device__ __forceinline__ bool tile_form(const StepArgs<R>& a, int64_t tile, co
 // registers until then.  One flag and one wave-uniform branch a tile, no
 // branches inside: at 17 divisions a cell (Euler, P = 3, limiter) a branch per
 // group of divisions cost 3% of the launch.
-template <int EQ, int P, bool LIM, class R>
-__device__ __forceinline__ bool tile_cells(const StepArgs<R>& a, int64_t tile, const TileIn<EQ, P, R>& in,
-                                          double lam, R nlam, int lane, double& smax, unsigned& flags,
+// fetch(in): the lane's old cell of the tile again.
+template <int EQ, int P, bool LIM, class R, class Fetch>
+__device__ __forceinline__ bool tile_cells(const Phys<R>& ph, int n_new, int tile, const TileIn<EQ, P, R>& in,
+                                          Fetch&& fetch, double lam, R nlam, int lane, double& smax, unsigned& flags,
                                           double (&pn)[ncomp<EQ>()], R (&dn)[ncomp<EQ>()][P + 1]) {
   constexpr bool divides = EQ == kEuler || (LIM && P >= 1);
   constexpr bool near = sizeof(R) == 8 && divides;
@@ -351,21 +352,21 @@ __device__ __forceinline__ bool tile_cells(const StepArgs<R>& a, int64_t tile, c
   unsigned fl = 0u;
   bool mine = false, ok = true;
   if constexpr (near) {
-    bool again = LIM && !near_eps(a.ph.eps);
+    bool again = LIM && !near_eps(ph.eps);
     if (!again) {
-      mine = tile_form<EQ, P, LIM, true>(a, tile, in, lam, nlam, lane, sp, fl, ok, pn, dn);
+      mine = tile_form<EQ, P, LIM, true>(ph, n_new, tile, in, lam, nlam, lane, sp, fl, ok, pn, dn);
       again = __ballot(!ok) != 0;
     }
     if (__builtin_expect(again, 0)) {
       asm volatile("" ::: "memory");
       TileIn<EQ, P, R> reread;
-      fetch_tile<EQ, P, R>(a, tile, lane, reread);
+      fetch(reread);
       sp = 0.0;
       fl = 0u;
-      mine = tile_form<EQ, P, LIM, false>(a, tile, reread, lam, nlam, lane, sp, fl, ok, pn, dn);
+      mine = tile_form<EQ, P, LIM, false>(ph, n_new, tile, reread, lam, nlam, lane, sp, fl, ok, pn, dn);
     }
   } else {
-    mine = tile_form<EQ, P, LIM, false>(a, tile, in, lam, nlam, lane, sp, fl, ok, pn, dn);
+    mine = tile_form<EQ, P, LIM, false>(ph, n_new, tile, in, lam, nlam, lane, sp, fl, ok, pn, dn);
   }
   flags |= fl;
   smax = __builtin_fmax(smax, sp);
@@ -379,7 +380,8 @@ __device__ __forceinline__ void compute_tile(const StepArgs<R>& a, int64_t tile,
   constexpr int NC = ncomp<EQ>();
   double pn[NC];
   R dn[NC][P + 1];
-  if (tile_cells<EQ, P, LIM, R>(a, tile, in, lam, nlam, lane, smax, flags, pn, dn)) {
+  auto reread = [&](TileIn<EQ, P, R>& x) { fetch_tile<EQ, P, R>(a, tile, lane, x); };
+  if (tile_cells<EQ, P, LIM, R>(a.ph, (int)a.n_new, (int)tile, in, reread, lam, nlam, lane, smax, flags, pn, dn)) {
     const int j = (int)tile * 63 + lane;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
