@@ -151,7 +151,7 @@ __device__ __forceinline__ void old_cell2(const double (&q)[ncomp<EQ>()][ndof(P)
           Fl[0][d] = h;
           Gl[0][d] = h;
         } else {
-          if (k == 0 && l == 0 && m == 0) rinv = wcc::div_rn(1.0, T[0].v[0][0][0]);
+          if (k == 0 && l == 0 && m == 0) rinv = wcc::rcp_rn(T[0].v[0][0][0]);
           u.v[k][l][m] = tquot3<P>(T[1], T[0], u, rinv, k, l, m);
           v.v[k][l][m] = tquot3<P>(T[2], T[0], v, rinv, k, l, m);
           const double kx = tprod3<P>(T[1], u, k, l, m);
@@ -273,9 +273,12 @@ __device__ __forceinline__ double js2d(const double (&D)[P + 1][P + 1]) {
 // The 2D limiter of Section 3.2 on one new cell (Eq. 2DLimitedPolynomial,
 // 2DLowOrderPolynomial, 2D2ndOrderWeights, high-order weights with sigma and
 // tau); D holds the unlimited scaled derivatives and is modified in place.
+// Its six divisions take the near forms (wcc_rn.hpp) and, where a lane with a
+// cell (`mine`) has an operand out of their ranges, the general ones in a
+// wave-uniform branch.
 template <int P>
 __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P + 1][P + 1], double vld, double vrd,
-                                        double vru, double vlu) {
+                                        double vru, double vlu, bool mine) {
   const double a2 = abar * 2.0;
   const double ux1 = a2 - (vld + vlu), uy1 = vlu - vld;
   const double ux2 = vrd - vld, uy2 = a2 - (vld + vrd);
@@ -284,12 +287,12 @@ __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P +
   const double b0 = js2d<P>(D);
   const double b1 = __builtin_fma(uy1, uy1, ux1 * ux1), b2 = __builtin_fma(uy2, uy2, ux2 * ux2);
   const double b3 = __builtin_fma(uy3, uy3, ux3 * ux3), b4 = __builtin_fma(uy4, uy4, ux4 * ux4);
-  double wh0, wh1, wh2, wh3, wh4;
-  if constexpr (P == 1) {
-    const double q0 = wcc::div_rn(1.0, b0 + eps), q1 = wcc::div_rn(1.0, b1 + eps), q2 = wcc::div_rn(1.0, b2 + eps),
-                 q3 = wcc::div_rn(1.0, b3 + eps), q4 = wcc::div_rn(1.0, b4 + eps);
-    wh0 = q0 * q0; wh1 = q1 * q1; wh2 = q2 * q2; wh3 = q3 * q3; wh4 = q4 * q4;
-  } else {
+  const double bm[5] = {b0, b1, b2, b3, b4};
+  double q[5];                                 // denominators of the candidates' weights
+#pragma unroll
+  for (int m = 0; m < 5; ++m) q[m] = P == 1 ? bm[m] + eps : __builtin_fma(bm[m], bm[m], eps);
+  double st = 1.0;                             // their common numerator
+  if constexpr (P > 1) {
     double p0 = abar;
 #pragma unroll
     for (int n = 2; n <= P; ++n)
@@ -318,13 +321,35 @@ __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P +
     double tau = D[0][P] * D[0][P];
 #pragma unroll
     for (int k = 1; k <= P; ++k) tau = __builtin_fma(D[k][P - k], D[k][P - k], tau);
-    const double st = sigma * tau;
-    const double r0 = wcc::div_rn(st, __builtin_fma(b0, b0, eps)), r1 = wcc::div_rn(st, __builtin_fma(b1, b1, eps)),
-                 r2 = wcc::div_rn(st, __builtin_fma(b2, b2, eps)), r3 = wcc::div_rn(st, __builtin_fma(b3, b3, eps)),
-                 r4 = wcc::div_rn(st, __builtin_fma(b4, b4, eps));
-    wh0 = __builtin_fma(r0, r0, 1.0); wh1 = r1 * r1; wh2 = r2 * r2; wh3 = r3 * r3; wh4 = r4 * r4;
+    st = sigma * tau;
   }
-  const double inv = wcc::div_rn(1.0, (((wh0 + wh1) + wh2) + wh3) + wh4);
+  double wh0, wh1, wh2, wh3, wh4;
+  auto form = [&](const double (&r)[5]) {
+    wh0 = P == 1 ? r[0] * r[0] : __builtin_fma(r[0], r[0], 1.0);
+    wh1 = r[1] * r[1]; wh2 = r[2] * r[2]; wh3 = r[3] * r[3]; wh4 = r[4] * r[4];
+    return (((wh0 + wh1) + wh2) + wh3) + wh4;
+  };
+  double r[5];
+  uint32_t qh = 0u, lo = 0u;
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    r[m] = wcc::rcp_near(q[m]);
+    if (P > 1) r[m] = wcc::div_near(st, q[m], r[m]);
+    qh = max(qh, wcc::hi_word(q[m]));
+    lo = max(lo, wcc::lo_word(q[m]));
+  }
+  const double sum = form(r);
+  double inv = wcc::rcp_near(sum);
+  lo = max(lo, wcc::lo_word(sum));
+  // q_m >= eps; a NaN's high word is above every bound
+  bool ok = (wcc::hi_word(eps) - wcc::hi_pow2(-900) < wcc::hi_pow2(0) - wcc::hi_pow2(-900)) &
+            (qh < wcc::hi_pow2(P == 1 ? 900 : 60)) & (lo != 0xffffffffu) & wcc::between_pow2(sum, -900, 900);
+  if (P > 1) ok &= wcc::near_num(st);
+  if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
+#pragma unroll
+    for (int m = 0; m < 5; ++m) r[m] = wcc::div_rn_any(st, q[m]);
+    inv = wcc::div_rn_any(1.0, form(r));
+  }
   const double w0 = wh0 * inv, w1 = wh1 * inv, w2_ = wh2 * inv, w3 = wh3 * inv, w4 = wh4 * inv;
   double dx1 = w0 * D[1][0], dy1 = w0 * D[0][1];
   dx1 = __builtin_fma(w1, ux1, dx1); dy1 = __builtin_fma(w1, uy1, dy1);
@@ -339,30 +364,76 @@ __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P +
     for (int l = 0; l <= n; ++l) D[n - l][l] = w0 * D[n - l][l];
 }
 
+// Velocity, pressure and sound speed of a conserved 2D Euler state; with CHAR
+// also the total enthalpy H and 1 / c.  Near divisions sharing 1 / rho, general
+// ones where a lane with a cell needs them.
+struct Gas2 {
+  double u, v, p, c, H, ic;
+};
+template <bool CHAR>
+__device__ __forceinline__ void gas2(const Phys2& ph, const double (&ab)[4], bool mine, Gas2& g) {
+  const double rho = ab[0], y = wcc::rcp_near(rho);
+  auto pressure = [&] { return ph.gm1 * (ab[3] - 0.5 * __builtin_fma(ab[2], g.v, ab[1] * g.u)); };
+  g.u = wcc::div_near(ab[1], rho, y);
+  g.v = wcc::div_near(ab[2], rho, y);
+  g.p = pressure();
+  const double gp = ph.gamma * g.p;
+  g.c = wcc::sqrt_near(wcc::div_near(gp, rho, y));
+  // the ranges of rho and gamma p put c^2 in [2^-460, 2^400]
+  bool ok = wcc::between_pow2(rho, -300, 60) & wcc::not_ones(rho) & wcc::near_num(ab[1]) & wcc::near_num(ab[2]) &
+            wcc::between_pow2(gp, -400, 100);
+  if (CHAR) {
+    const double h = ab[3] + g.p;
+    g.H = wcc::div_near(h, rho, y);
+    g.ic = wcc::rcp_near(g.c);
+    ok &= wcc::between_pow2(h, -400, 100) & wcc::not_ones(g.c);
+  }
+  if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
+    g.u = wcc::div_rn_any(ab[1], rho);
+    g.v = wcc::div_rn_any(ab[2], rho);
+    g.p = pressure();
+    g.c = wcc::sqrt_rn_any(wcc::div_rn_any(ph.gamma * g.p, rho));
+    if (CHAR) {
+      g.H = wcc::div_rn_any(ab[3] + g.p, rho);
+      g.ic = wcc::div_rn_any(1.0, g.c);
+    }
+  }
+}
+
 // Rotated characteristic limiting of a 2D Euler new cell (Section 4): the
 // direction n = grad(phi)/|grad(phi)| with phi = rho e from the new cell's
 // central-difference derivatives (Eq. RotatedNormal; n = (1, 0) where the
 // gradient vanishes); the eigenvectors of A cos(theta) + B sin(theta) at the
-// new average; every characteristic field through limit2d; back with R.
-// v[c][vtx]: vertex values, vtx = LD, RD, RU, LU.
+// new average (gas state g); every characteristic field through limit2d; back
+// with R.  v[c][vtx]: vertex values, vtx = LD, RD, RU, LU.  idx, idy: 1 / dx
+// and 1 / dy, correctly rounded.
 template <int P>
-__device__ __forceinline__ void char_limit2d(const Phys2& ph, double dx, double dy, const double (&ab)[4],
+__device__ __forceinline__ void char_limit2d(const Phys2& ph, double dx, double dy, double idx, double idy,
+                                             const double (&ab)[4], const Gas2& g, bool mine,
                                              double (&D)[4][P + 1][P + 1], const double (&v)[4][4]) {
-  const double gx = wcc::div_rn(D[3][1][0], dx), gy = wcc::div_rn(D[3][0][1], dy);
-  const double g2 = __builtin_fma(gy, gy, gx * gx);
-  double nx = 1.0, ny = 0.0;
-  if (g2 > 0.0) {
-    const double gn = wcc::sqrt_rn(g2);
-    nx = wcc::div_rn(gx, gn);
-    ny = wcc::div_rn(gy, gn);
+  const double ex = D[3][1][0], ey = D[3][0][1];
+  double nx, ny;
+  {
+    const double gx = wcc::div_near(ex, dx, idx), gy = wcc::div_near(ey, dy, idy);
+    const double g2 = __builtin_fma(gy, gy, gx * gx);
+    const double gn = wcc::sqrt_near(g2), y = wcc::rcp_near(gn);
+    const bool some = g2 > 0.0;
+    nx = some ? wcc::div_near(gx, gn, y) : 1.0;
+    ny = some ? wcc::div_near(gy, gn, y) : 0.0;
+    const bool ok = wcc::near_den(dx) & wcc::near_den(dy) & wcc::near_num(ex) & wcc::near_num(ey) &
+                    ((g2 == 0.0) | (wcc::between_pow2(g2, -300, 100) & wcc::not_ones(gn) & wcc::near_num(gx) &
+                                    wcc::near_num(gy)));
+    if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
+      const double hx = wcc::div_rn_any(ex, dx), hy = wcc::div_rn_any(ey, dy);
+      const double h2 = __builtin_fma(hy, hy, hx * hx), hn = wcc::sqrt_rn_any(h2);
+      const bool any = h2 > 0.0;
+      nx = any ? wcc::div_rn_any(hx, hn) : 1.0;
+      ny = any ? wcc::div_rn_any(hy, hn) : 0.0;
+    }
   }
-  const double rho = ab[0], u = wcc::div_rn(ab[1], rho), vv = wcc::div_rn(ab[2], rho);
-  const double p = ph.gm1 * (ab[3] - 0.5 * __builtin_fma(ab[2], vv, ab[1] * u));
-  const double c = wcc::sqrt_rn(wcc::div_rn(ph.gamma * p, rho));
-  const double H = wcc::div_rn(ab[3] + p, rho);
+  const double u = g.u, vv = g.v, c = g.c, H = g.H, ic = g.ic;
   const double un = __builtin_fma(vv, ny, u * nx), ut = __builtin_fma(vv, nx, -(u * ny));
   const double q2 = __builtin_fma(vv, vv, u * u);
-  const double ic = wcc::div_rn(1.0, c);
   const double b1 = ph.gm1 * (ic * ic), b2 = 0.5 * (q2 * b1);
   const double uic = un * ic, nxic = nx * ic, nyic = ny * ic, b1u = b1 * u, b1v = b1 * vv;
   const double L[4][4] = {{0.5 * (b2 + uic), -0.5 * (b1u + nxic), -0.5 * (b1v + nyic), 0.5 * b1},
@@ -393,7 +464,7 @@ __device__ __forceinline__ void char_limit2d(const Phys2& ph, double dx, double 
     for (int n = 1; n <= P; ++n)
 #pragma unroll
       for (int l = 0; l <= n; ++l) cD[n - l][l] = proj(D[0][n - l][l], D[1][n - l][l], D[2][n - l][l], D[3][n - l][l]);
-    limit2d<P>(ph.eps, ca, cD, cv[0], cv[1], cv[2], cv[3]);
+    limit2d<P>(ph.eps, ca, cD, cv[0], cv[1], cv[2], cv[3], mine);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       if (f == 2 && r == 0) continue;
@@ -467,23 +538,19 @@ __device__ __forceinline__ double point_value(double abar, const double (&D)[P +
   return pv;
 }
 
-// Wave-speed rate s_x/dx + s_y/dy of a conserved average; status bit 2 for a
-// non-positive density or pressure.
+// Wave-speed rate s_x/dx + s_y/dy of a conserved average (Euler: of gas state
+// g); status bit 2 for a non-positive density or pressure.
 template <int EQ>
-__device__ __forceinline__ double speed_rate(const double (&ab)[ncomp<EQ>()], const Phys2& ph, double idx,
-                                             double idy, unsigned& flag) {
+__device__ __forceinline__ double speed_rate(const double (&ab)[ncomp<EQ>()], const Gas2& g, const Phys2& ph,
+                                             double idx, double idy, unsigned& flag) {
   if constexpr (EQ == kAdvection) {
     return __builtin_fma(__builtin_fabs(ph.b), idy, __builtin_fabs(ph.a) * idx);
   } else if constexpr (EQ == kBurgers) {
     const double s = __builtin_fabs(ab[0]);
     return __builtin_fma(s, idy, s * idx);
   } else {
-    const double rho = ab[0];
-    const double u = wcc::div_rn(ab[1], rho), v = wcc::div_rn(ab[2], rho);
-    const double p = ph.gm1 * (ab[3] - 0.5 * __builtin_fma(ab[2], v, ab[1] * u));
-    const double c = wcc::sqrt_rn(wcc::div_rn(ph.gamma * p, rho));
-    if (!(rho > 0.0) || !(p > 0.0)) flag |= 2u;
-    return __builtin_fma(__builtin_fabs(v) + c, idy, (__builtin_fabs(u) + c) * idx);
+    if (!(ab[0] > 0.0) || !(g.p > 0.0)) flag |= 2u;
+    return __builtin_fma(__builtin_fabs(g.v) + g.c, idy, (__builtin_fabs(g.u) + g.c) * idx);
   }
 }
 

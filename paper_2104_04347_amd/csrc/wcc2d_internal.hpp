@@ -21,6 +21,9 @@ struct Step2Args {
   int32_t periodic_y;
   int32_t parity_old;     // 0: original -> staggered mesh, 1: back
   int32_t slot;           // ring slot of this launch
+  int32_t strips;         // 64-column strips of the new mesh (row-marching kernels; set by the launcher)
+  int32_t bands;          // bands of rows (band-major items), or 0: runs of strip-major (strip, row) units
+  int32_t share, extra;   // rows of a band (units of a run): share, and one more in the first `extra`
   double dx, dy;
   double idx, idy;        // 1/dx, 1/dy
   double dt_fixed;        // > 0: fixed dt instead of the CFL step

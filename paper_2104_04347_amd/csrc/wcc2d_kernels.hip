@@ -10,6 +10,8 @@
 // partial slots.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "wcc2d_cell.hpp"
 #include "wcc2d_internal.hpp"
 #include "wcc_tile.hpp"
@@ -139,6 +141,7 @@ __device__ __forceinline__ void new_cell2(const Step2Args& a, Gather&& gather, S
                                           double hy, double& smax, unsigned& flags) {
   constexpr int NC = ncomp<EQ>();
   double ab[NC];
+  Gas2 gas{};
   if constexpr (EQ == kEuler && LIM && P >= 1) {
     // the characteristic limiter couples the components: form all four new
     // averages and derivatives first
@@ -154,7 +157,8 @@ __device__ __forceinline__ void new_cell2(const Step2Args& a, Gather&& gather, S
       vx[c][2] = g.VE[0];
       vx[c][3] = g.VB[0];
     }
-    char_limit2d<P>(a.ph, a.dx, a.dy, ab, D, vx);
+    gas2<true>(a.ph, ab, mine, gas);
+    char_limit2d<P>(a.ph, a.dx, a.dy, a.idx, a.idy, ab, gas, mine, D, vx);
     if (mine) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) store(c, point_value<P>(ab[c], D[c]), D[c], flags);
@@ -168,13 +172,14 @@ __device__ __forceinline__ void new_cell2(const Step2Args& a, Gather&& gather, S
       ab[c] = abar;
       double D[P + 1][P + 1];
       if constexpr (P >= 1) new_derivatives<P>(g.VA, g.VB, g.VC, g.VE, D);
-      if constexpr (LIM && P >= 1) limit2d<P>(a.ph.eps, abar, D, g.VA[0], g.VC[0], g.VE[0], g.VB[0]);
+      if constexpr (LIM && P >= 1) limit2d<P>(a.ph.eps, abar, D, g.VA[0], g.VC[0], g.VE[0], g.VB[0], mine);
       const double pv = point_value<P>(abar, D);
       if (mine) store(c, pv, D, flags);
     }
   }
+  if constexpr (EQ == kEuler && !(LIM && P >= 1)) gas2<false>(a.ph, ab, mine, gas);
   if (mine) {
-    const double sr = speed_rate<EQ>(ab, a.ph, a.idx, a.idy, flags);
+    const double sr = speed_rate<EQ>(ab, gas, a.ph, a.idx, a.idy, flags);
     if (!__builtin_isfinite(sr)) flags |= 1u;
     smax = __builtin_fmax(smax, sr);
   }
@@ -322,64 +327,74 @@ __global__ __launch_bounds__(256) void k2d_half_step_rows(const Step2Args a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
             nw = blockDim.x >> 6;
   RowCarry<EQ, P>& carry = carry_all[wave];
-  const int strips = (a.nxn + 62) / 63, rows = a.nyn;
-  const int64_t units = (int64_t)strips * rows, waves = (int64_t)gridDim.x * nw;
-  const int64_t gw = (int64_t)blockIdx.x * nw + wave;
-  int u_begin = (int)(gw * units / waves), u_end = (int)((gw + 1) * units / waves);
-  if (BANDS && waves >= strips) {
+  const wcc::StepIn ring = wcc::step_load(a.ctrl, a.parts, a.slot);
+  const int rows = a.nyn;
+  // this wave's run: `left` new rows from row r of strip sx
+  int sx = 0, r = 0, left = 0;
+  if (BANDS && a.bands > 0) {
     const int G = (int)gridDim.x;
     const int lb = (G & 7) == 0 ? (int)(blockIdx.x & 7) * (G >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-    const int64_t item = (int64_t)lb * nw + wave;
-    const int bands = (int)(waves / strips);
-    u_begin = u_end = 0;
-    if (item < (int64_t)bands * strips) {
-      const int band = (int)(item / strips), sx = (int)(item - (int64_t)band * strips);
-      u_begin = sx * rows + (int)((int64_t)band * rows / bands);
-      u_end = sx * rows + (int)((int64_t)(band + 1) * rows / bands);
+    const unsigned item = (unsigned)(lb * nw + wave), band = item / (unsigned)a.strips;
+    if (band < (unsigned)a.bands) {
+      sx = (int)(item - band * (unsigned)a.strips);
+      r = (int)band * a.share + min((int)band, a.extra);
+      left = a.share + ((int)band < a.extra ? 1 : 0);
     }
+  } else {
+    const int gw = (int)blockIdx.x * nw + wave;
+    const int u = gw * a.share + min(gw, a.extra);
+    left = a.share + (gw < a.extra ? 1 : 0);
+    sx = u / rows;
+    r = u - sx * rows;
   }
+  const int off = a.parity_old == 0 ? 0 : -1;
+  // old row y under the strip's columns
+  auto load_row = [&](int strip, int y, double (&x)[NC][ND]) {
+    load_old<EQ, P, BUF>(a, map_idx(63 * strip + lane + off, a.nxo, a.periodic_x),
+                         map_idx(y + off, a.nyo, a.periodic_y), x);
+  };
+  double qn[NC][ND];
+  if (PF && left > 0) load_row(sx, r, qn);
   double dt;
-  if (!wcc::step_time(wcc::step_load(a.ctrl, a.parts, a.slot), a.ctrl, a.parts, a.slot, 1.0, a.dt_fixed,
-                      blockIdx.x == 0 && wave == 0, dt))
-    return;
+  if (!wcc::step_time(ring, a.ctrl, a.parts, a.slot, 1.0, a.dt_fixed, blockIdx.x == 0 && wave == 0, dt)) return;
   const double lamx = wcc::div_rn(dt, a.dx), lamy = wcc::div_rn(dt, a.dy);
   const double nlx = -lamx, nly = -lamy, hx = 0.5 * lamx, hy = 0.5 * lamy;
-  const int off = a.parity_old == 0 ? 0 : -1;
   double smax = 0.0;
   unsigned flags = 0u;
-  double qn[NC][ND];
-  if (PF && u_begin < u_end) {
-    const int sx = u_begin / rows, r = u_begin - sx * rows;
-    load_old<EQ, P, BUF>(a, map_idx(63 * sx + lane + off, a.nxo, a.periodic_x), map_idx(r + 1 + off, a.nyo, a.periodic_y),
-                         qn);
-  }
-  for (int u = u_begin; u < u_end; ++u) {
-    const int sx = u / rows, r = u - sx * rows;
-    const int i = map_idx(63 * sx + lane + off, a.nxo, a.periodic_x);
-    if (u == u_begin || r == 0) {
-      // lower parents of new row r: the old row below, expanded afresh
-      Old2<EQ, P> o;
-      old_of<EQ, P, BUF>(a, i, map_idx(r + off, a.nyo, a.periodic_y), nlx, nly, o);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) put_carry<EQ, P>(carry, c, lane, o);
-    }
+  // One old row a turn: the first of a run (and of a strip a run enters) only
+  // leaves its expansion as the lower parents of the next turn's new row.
+  // Every old row goes through the same code and the same prefetch; with the
+  // first rows expanded by a copy of their own, each wave waited for a load it
+  // had not issued ahead, and the loop's code was half as long again.  The row
+  // kernels are bound by issue and by the latency of dependent binary64 chains
+  // at one wave per SIMD (Euler).  With the near divisions of the limiter, us a
+  // half-step before and after: Burgers 1024 x 1024 41.9 and 38.9, unlimited
+  // Euler 768 x 768 104.9 and 102.2, limited Euler 600 x 600 78.5 and 71.2
+  // (P = 3).
+  bool prime = true;
+  while (left > 0) {
     double q[NC][ND];
+    const int turn = left - (prime ? 0 : 1);            // new rows left after this turn
+    const bool wrapped = !prime && r + 1 == rows;       // the run goes on in the next strip
+    const int sx2 = wrapped ? sx + 1 : sx, r2 = wrapped ? 0 : (prime ? r : r + 1);
     if constexpr (PF) {
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int d = 0; d < ND; ++d) q[c][d] = qn[c][d];
-      if (u + 1 < u_end) {
-        const int sx2 = (u + 1) / rows, r2 = u + 1 - sx2 * rows;
-        load_old<EQ, P, BUF>(a, map_idx(63 * sx2 + lane + off, a.nxo, a.periodic_x),
-                             map_idx(r2 + 1 + off, a.nyo, a.periodic_y), qn);
-      }
+      if (turn > 0) load_row(sx2, wrapped ? 0 : r2 + 1, qn);
       __builtin_amdgcn_sched_barrier(0);
     } else {
-      load_old<EQ, P, BUF>(a, i, map_idx(r + 1 + off, a.nyo, a.periodic_y), q);
+      load_row(sx, prime ? r : r + 1, q);
     }
     Old2<EQ, P> o;
     old_cell2<EQ, P>(q, nlx, nly, a.ph, o);
+    if (prime) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) put_carry<EQ, P>(carry, c, lane, o);
+      prime = false;
+      continue;
+    }
     const int ni = 63 * sx + lane;
     const bool mine = lane < 63 && ni < a.nxn;
     auto gather = [&](int c, Par2<P>& g) {
@@ -407,6 +422,10 @@ __global__ __launch_bounds__(256) void k2d_half_step_rows(const Step2Args a) {
       store_cell<EQ, P, BUF>(a, c, ncell, pv, D, fl);
     };
     new_cell2<EQ, P, LIM>(a, gather, store, mine, hx, hy, smax, flags);
+    left = turn;
+    sx = sx2;
+    r = r2;
+    prime = wrapped;
   }
   wcc::publish(a.ctrl, a.parts, a.slot, smax, flags);
 }
@@ -437,7 +456,9 @@ __global__ __launch_bounds__(256) void k2d_state_speed(const Step2Args a) {
       ab[c] = s;
     }
     if (!ok) flags |= 1u;
-    const double sr = speed_rate<EQ>(ab, a.ph, a.idx, a.idy, flags);
+    Gas2 gas{};
+    if constexpr (EQ == kEuler) gas2<false>(a.ph, ab, true, gas);
+    const double sr = speed_rate<EQ>(ab, gas, a.ph, a.idx, a.idy, flags);
     smax = __builtin_fmax(smax, sr);
   }
   wcc::publish(a.ctrl, a.parts, a.slot == 0 ? 2 : a.slot - 1, smax, flags);
@@ -446,7 +467,15 @@ __global__ __launch_bounds__(256) void k2d_state_speed(const Step2Args a) {
 // Variants 2 and 3 take the buffer-addressed kernel when a state buffer is
 // below 2 GiB; variant 1 and larger states the pointer form.
 template <int EQ, int P, bool LIM>
-static hipError_t launch_epl(const Step2Args& a, int variant, int blocks, int threads, hipStream_t s) {
+static hipError_t launch_epl(Step2Args a, int variant, int blocks, int threads, hipStream_t s) {
+  // the waves' shares of the rows, divided here so that no launch starts with
+  // 64-bit divisions
+  const int64_t waves = (int64_t)blocks * (threads / 64), units = (int64_t)((a.nxn + 62) / 63) * a.nyn;
+  a.strips = (a.nxn + 62) / 63;
+  a.bands = variant == 3 && waves >= a.strips ? (int32_t)std::min<int64_t>(waves / a.strips, 1 << 30) : 0;
+  const int64_t whole = a.bands > 0 ? a.nyn : units, parts = a.bands > 0 ? a.bands : waves;
+  a.share = (int32_t)(whole / parts);
+  a.extra = (int32_t)(whole % parts);
   const bool buf = buffer_form((int64_t)ncomp<EQ>() * ndof(P) * a.plane);
   if (variant == 3 && buf)
     hipLaunchKernelGGL((k2d_half_step_rows<EQ, P, LIM, true, true, true>), dim3(blocks), dim3(threads), 0, s, a);

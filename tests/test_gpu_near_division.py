@@ -67,3 +67,34 @@ def test_denominators_of_ones():
         s.run(30, 0.25)
         q, _ = s.read()
     assert np.array_equal(q, ref.q)
+
+
+@pytest.mark.parametrize("eq,P,scale,eps", [
+    ("euler", 3, 1.0, 1e-40), ("euler", 2, 2.0 ** 60, 1e-40), ("euler", 1, 1e-95, 1e-40), ("euler", 2, 1.0, 0.0),
+    ("burgers", 3, 1e-62, 1e-40), ("burgers", 2, 1e9, 1e-40), ("burgers", 1, 1e70, 1e-40),
+    ("advection", 3, 1.0, 1e-290)])
+@pytest.mark.parametrize("limiter", [True, False])
+def test_out_of_range_operands_2d(eq, P, scale, eps, limiter):
+    """The same in 2D, where each group of divisions has a general form of its own (some lanes need it, or all)."""
+    from paper_2104_04347_amd import binding
+    if eq == "euler":
+        nx, ny, bc, dom = 70, 21, "transmissive", (-1.0, 1.0, -1.0, 1.0)
+        X, Y = inputs.centers2d(*dom, nx, ny, 0, bc)
+        rho = 1.0 + 0.3 * (X > 0.1) + 0.2 * (Y > -0.2)
+        u, v, p = 0.2 * (Y > 0), -0.1 * (X < 0.3), 1.0 + 0.5 * (X + Y > 0)
+        q0 = np.zeros((4, inputs.ndof2d(P)) + X.shape)
+        q0[:, 0] = np.stack([rho, rho * u, rho * v, p / 0.4 + 0.5 * rho * (u * u + v * v)]) * scale
+    else:
+        nx, ny, bc, dom = 70, 21, "periodic", (0.0, 2.0, 0.0, 2.0)
+        q0 = inputs.taylor2d(inputs.modes2d(3), P, nx, ny) * scale
+    box = dict(zip(("x_left", "x_right", "y_left", "y_right"), dom))
+    with np.errstate(all="ignore"):
+        ref = oracle.run2d(oracle.Problem2D(eq, P, nx, ny, limiter=limiter, bc=bc, eps=eps, **box), q0, cfl=0.2,
+                           max_half_steps=7)
+    s = binding.Solver2D(eq, P, nx, ny, limiter=limiter, bc=bc, eps=eps, **box)
+    s.write(q0)
+    s.run(7, 0.2)
+    q, info = s.read()
+    s.close()
+    assert info.t == ref.t
+    assert np.array_equal(q, ref.q, equal_nan=True)
