@@ -293,10 +293,10 @@ int wcc_batch_read_dofs(wcc_batch* bt, int b, double* host, int64_t cap, wcc_sta
  * (0 keeps the current one; 1 = fused: one launch per half-step over all
  * tiles, degree switched per tile; 2 = grouped: one launch per degree per
  * half-step; 3 and 4 = fused and grouped with the new cells staged in LDS and
- * stored in whole 64-cell groups; 5 (the default) and 6 = grouped with direct
- * / staged stores, the degrees' launches captured as parallel branches of the
- * run's graphs so that they may overlap on the device; other values return
- * WCC_EINVAL). */
+ * stored in whole 64-cell groups; 5 and 6 = grouped with direct / staged
+ * stores, the degrees' launches captured as parallel branches of the run's
+ * graphs so that they may overlap on the device; other values return
+ * WCC_EINVAL).  Until this is called: 5 in binary64, 6 FP32-mixed. */
 int wcc_batch_set_schedule(wcc_batch* bt, int threads_per_block, int blocks, int mode);
 /* Device time of the last wcc_batch_advance call, in ms (waits for it). */
 int wcc_batch_last_run_ms(wcc_batch* bt, double* ms);

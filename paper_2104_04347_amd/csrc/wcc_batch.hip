@@ -76,40 +76,47 @@ __device__ __forceinline__ StepArgs<R> instance_args(const BatchArgs<R>& a, cons
   return s;
 }
 
-template <int EQ, int P, bool LIM, class R>
-__device__ __forceinline__ void batch_tile(const BatchArgs<R>& a, const BatchInst& in, int first, int bc,
-                                           Ctrl* ctrl, int lane, double& smax, unsigned& flags) {
+// What a wave keeps of the instance whose tiles it is walking: the
+// single-instance view of it, and this half-step's lambda (or go = false: the
+// instance is finished).  Formed when the wave enters the instance: a wave
+// takes every nw-th tile, so that is its first tile of it, and the tile with
+// first == 0 is always seen that way (it leads the instance's ring).  Formed
+// again for every tile, the three dependent reads (tile, instance, ring) and
+// the division stood before each tile's loads: 512 instances of 256 to 65,536
+// cells, us a half-step before and now: FP32-mixed staged 175.0 and 155.5,
+// direct 174.9 and 165.2; binary64 direct 256 and 236.  (Loading the wave's
+// next tile ahead as well gained 2% there and lost 5-8% at a tenth of the
+// cells, for the registers.)
+template <class R>
+struct Current {
+  StepArgs<R> s;
+  double lam;
+  bool go;
+};
+
+template <class R>
+__device__ __forceinline__ void enter_instance(const BatchArgs<R>& a, const BatchTile& tl, int bc, Current<R>& c) {
+  const BatchInst in = a.inst[tl.inst];
+  Ctrl* ctrl = a.ctrl + tl.inst;
   double dt;
-  const bool go = step_time(step_load(ctrl, nullptr, a.slot), ctrl, nullptr, a.slot, in.dx, 0.0, first == 0, dt);
-  if (!go) return;
-  const StepArgs<R> s = instance_args(a, in, bc, ctrl);
-  const double lam = div_rn(dt, in.dx);
-  if ((int64_t)first * 63 < s.n_new) run_tile<EQ, P, LIM, R>(s, first, lam, (R)(-lam), lane, smax, flags);
+  c.go = step_time(step_load(ctrl, nullptr, a.slot), ctrl, nullptr, a.slot, in.dx, 0.0, tl.first == 0, dt);
+  c.s = instance_args(a, in, bc, ctrl);
+  c.lam = div_rn(dt, in.dx);
 }
 
-// Staged form: the tile's new cells go to the wave's LDS region; [lo, hi)
-// returns the cells staged (empty when the instance is finished or the tile
-// lies beyond this mesh's last cell).
+// Staged form: the tile's new cells go to the wave's LDS region.
 template <int EQ, int P, bool LIM, class R, class S>
-__device__ __forceinline__ void batch_tile_staged(const BatchArgs<R>& a, const BatchInst& in, int first, int bc,
-                                                  Ctrl* ctrl, int lane, int wave, S& st, double& smax,
-                                                  unsigned& flags, int& lo, int& hi) {
+__device__ __forceinline__ void batch_tile_staged(const Current<R>& c, int first, int lane, int wave, S& st,
+                                                  double& smax, unsigned& flags) {
   constexpr int NC = ncomp<EQ>();
-  double dt;
-  const bool go = step_time(step_load(ctrl, nullptr, a.slot), ctrl, nullptr, a.slot, in.dx, 0.0, first == 0, dt);
-  if (!go) return;
-  const StepArgs<R> s = instance_args(a, in, bc, ctrl);
-  const double lam = div_rn(dt, in.dx);
-  if ((int64_t)first * 63 >= s.n_new) return;
   TileIn<EQ, P, R> ti;
-  fetch_tile<EQ, P, R>(s, first, lane, ti);
+  fetch_tile<EQ, P, R>(c.s, first, lane, ti);
   double pn[NC];
   R dn[NC][P + 1];
-  auto reread = [&](TileIn<EQ, P, R>& x) { fetch_tile<EQ, P, R>(s, first, lane, x); };
-  if (tile_cells<EQ, P, LIM, R>(s.ph, (int)s.n_new, first, ti, reread, lam, (R)(-lam), lane, smax, flags, pn, dn))
+  auto reread = [&](TileIn<EQ, P, R>& x) { fetch_tile<EQ, P, R>(c.s, first, lane, x); };
+  if (tile_cells<EQ, P, LIM, R>(c.s.ph, (int)c.s.n_new, first, ti, reread, c.lam, (R)(-c.lam), lane, smax, flags, pn,
+                                dn))
     stage_put<EQ, P, R>(st, wave * 64 + lane, pn, dn);
-  lo = first * 63;
-  hi = lo + 63 < (int)s.n_new ? lo + 63 : (int)s.n_new;
 }
 
 // P < 0: fused schedule (switch on the instance's degree); P >= 0: the
@@ -131,25 +138,32 @@ void k_batch_step(const BatchArgs<R> a, const int64_t* __restrict__ block_start,
   int cur = -1;
   double smax = 0.0;
   unsigned flags = 0u;
+  Current<R> c;
+  // the wave's next tile: publishes the instance it leaves, enters the one it
+  // comes to; whether the tile has cells to compute
+  auto take = [&](const BatchTile& tl) {
+    if (tl.inst != cur) {
+      if (cur >= 0) publish_wave(a.ctrl + cur, a.slot, smax, flags);
+      cur = tl.inst;
+      smax = 0.0;
+      flags = 0u;
+      enter_instance(a, tl, bc, c);
+    }
+    return c.go && tl.first * 63 < (int)c.s.n_new;
+  };
   if constexpr (!STG) {
     for (int64_t w = t0 + wave; w < t1; w += nw) {
       const BatchTile tl = a.tiles[w];
-      if (tl.inst != cur) {
-        if (cur >= 0) publish_wave(a.ctrl + cur, a.slot, smax, flags);
-        cur = tl.inst;
-        smax = 0.0;
-        flags = 0u;
-      }
-      const BatchInst in = a.inst[tl.inst];
-      Ctrl* ctrl = a.ctrl + tl.inst;
+      if (!take(tl)) continue;
+      const R nlam = (R)(-c.lam);
       if constexpr (PSEL >= 0) {
-        batch_tile<EQ, PSEL, LIM, R>(a, in, tl.first, bc, ctrl, lane, smax, flags);
+        run_tile<EQ, PSEL, LIM && PSEL != 0, R>(c.s, tl.first, c.lam, nlam, lane, smax, flags);
       } else {
-        switch (in.P) {
-          case 0: batch_tile<EQ, 0, false, R>(a, in, tl.first, bc, ctrl, lane, smax, flags); break;
-          case 1: batch_tile<EQ, 1, LIM, R>(a, in, tl.first, bc, ctrl, lane, smax, flags); break;
-          case 2: batch_tile<EQ, 2, LIM, R>(a, in, tl.first, bc, ctrl, lane, smax, flags); break;
-          default: batch_tile<EQ, 3, LIM, R>(a, in, tl.first, bc, ctrl, lane, smax, flags); break;
+        switch (a.inst[tl.inst].P) {
+          case 0: run_tile<EQ, 0, false, R>(c.s, tl.first, c.lam, nlam, lane, smax, flags); break;
+          case 1: run_tile<EQ, 1, LIM, R>(c.s, tl.first, c.lam, nlam, lane, smax, flags); break;
+          case 2: run_tile<EQ, 2, LIM, R>(c.s, tl.first, c.lam, nlam, lane, smax, flags); break;
+          default: run_tile<EQ, 3, LIM, R>(c.s, tl.first, c.lam, nlam, lane, smax, flags); break;
         }
       }
     }
@@ -162,34 +176,21 @@ void k_batch_step(const BatchArgs<R> a, const int64_t* __restrict__ block_start,
       const int64_t w = wb + wave;
       int lo = 0, hi = 0, P = 0;
       BatchTile tl{0, 0};
-      BatchInst in{};
       if (w < t1) {
         tl = a.tiles[w];
-        if (tl.inst != cur) {
-          if (cur >= 0) publish_wave(a.ctrl + cur, a.slot, smax, flags);
-          cur = tl.inst;
-          smax = 0.0;
-          flags = 0u;
-        }
-        in = a.inst[tl.inst];
-        Ctrl* ctrl = a.ctrl + tl.inst;
-        P = PSEL >= 0 ? PSEL : in.P;
-        if constexpr (PSEL >= 0) {
-          batch_tile_staged<EQ, PSEL, LIM, R>(a, in, tl.first, bc, ctrl, lane, wave, st, smax, flags, lo, hi);
-        } else {
-          switch (in.P) {
-            case 0:
-              batch_tile_staged<EQ, 0, false, R>(a, in, tl.first, bc, ctrl, lane, wave, st, smax, flags, lo, hi);
-              break;
-            case 1:
-              batch_tile_staged<EQ, 1, LIM, R>(a, in, tl.first, bc, ctrl, lane, wave, st, smax, flags, lo, hi);
-              break;
-            case 2:
-              batch_tile_staged<EQ, 2, LIM, R>(a, in, tl.first, bc, ctrl, lane, wave, st, smax, flags, lo, hi);
-              break;
-            default:
-              batch_tile_staged<EQ, 3, LIM, R>(a, in, tl.first, bc, ctrl, lane, wave, st, smax, flags, lo, hi);
-              break;
+        if (take(tl)) {
+          lo = tl.first * 63;
+          hi = lo + 63 < (int)c.s.n_new ? lo + 63 : (int)c.s.n_new;
+          if constexpr (PSEL >= 0) {
+            batch_tile_staged<EQ, PSEL, LIM && PSEL != 0, R>(c, tl.first, lane, wave, st, smax, flags);
+          } else {
+            P = a.inst[tl.inst].P;
+            switch (P) {
+              case 0: batch_tile_staged<EQ, 0, false, R>(c, tl.first, lane, wave, st, smax, flags); break;
+              case 1: batch_tile_staged<EQ, 1, LIM, R>(c, tl.first, lane, wave, st, smax, flags); break;
+              case 2: batch_tile_staged<EQ, 2, LIM, R>(c, tl.first, lane, wave, st, smax, flags); break;
+              default: batch_tile_staged<EQ, 3, LIM, R>(c, tl.first, lane, wave, st, smax, flags); break;
+            }
           }
         }
       }
@@ -204,19 +205,16 @@ void k_batch_step(const BatchArgs<R> a, const int64_t* __restrict__ block_start,
         if (w + 1 < t1) {
           // the next tile continues the run only if it has cells on this mesh
           const BatchTile tn = a.tiles[w + 1];
-          const int64_t n_new = a.parity_old == 0 ? in.N : (bc == kPeriodic ? in.N : in.N + 1);
-          next = tn.inst == tl.inst && tn.first == tl.first + 1 && (int64_t)tn.first * 63 < n_new;
+          next = tn.inst == tl.inst && tn.first == tl.first + 1 && tn.first * 63 < (int)c.s.n_new;
         }
-        double* p_new = a.p_out + in.p_off;
-        R* d_new = a.d_out + in.d_off;
         if constexpr (PSEL >= 0) {
-          stage_flush<EQ, PSEL, R>(st, side, wave, nw, lane, lo, hi, prev, next, p_new, d_new, in.ld);
+          stage_flush<EQ, PSEL, R>(st, side, wave, nw, lane, lo, hi, prev, next, c.s.p_new, c.s.d_new, c.s.ld);
         } else {
           switch (P) {
-            case 0: stage_flush<EQ, 0, R>(st, side, wave, nw, lane, lo, hi, prev, next, p_new, d_new, in.ld); break;
-            case 1: stage_flush<EQ, 1, R>(st, side, wave, nw, lane, lo, hi, prev, next, p_new, d_new, in.ld); break;
-            case 2: stage_flush<EQ, 2, R>(st, side, wave, nw, lane, lo, hi, prev, next, p_new, d_new, in.ld); break;
-            default: stage_flush<EQ, 3, R>(st, side, wave, nw, lane, lo, hi, prev, next, p_new, d_new, in.ld); break;
+            case 0: stage_flush<EQ, 0, R>(st, side, wave, nw, lane, lo, hi, prev, next, c.s.p_new, c.s.d_new, c.s.ld); break;
+            case 1: stage_flush<EQ, 1, R>(st, side, wave, nw, lane, lo, hi, prev, next, c.s.p_new, c.s.d_new, c.s.ld); break;
+            case 2: stage_flush<EQ, 2, R>(st, side, wave, nw, lane, lo, hi, prev, next, c.s.p_new, c.s.d_new, c.s.ld); break;
+            default: stage_flush<EQ, 3, R>(st, side, wave, nw, lane, lo, hi, prev, next, c.s.p_new, c.s.d_new, c.s.ld); break;
           }
         }
       }
@@ -311,7 +309,7 @@ struct wcc_batch {
   int64_t p_total = 0, d_total = 0;      // elements per buffer
   // schedule
   bool grouped = true;
-  bool staged = false;                   // line-aligned stores through LDS
+  bool staged = false;                   // line-aligned stores through LDS (default: FP32-mixed, see wcc_batch_create)
   bool branches = true;                  // grouped: the degrees' launches as parallel graph branches
   int threads = 256, blocks = 0, cu = 256;
   std::vector<int64_t> block_start;      // fused: blocks+1 entries; grouped: per group blocks+1 entries, concatenated
@@ -585,6 +583,11 @@ int wcc_batch_create(int equation, int B, const int32_t* P, const int64_t* N, in
   b->B = B;
   b->prm = prm;
   b->elem = prm.precision == WCC_FP64 ? 8 : 4;
+  // Parallel degree branches, with staged stores in the FP32-mixed mode: 512
+  // instances (7M cells) 155 against 165 us a half-step, 64 (0.7M) 26 against
+  // 33, 16 (40k) alike.  In binary64 the staging area leaves too few waves:
+  // 310 against 236 and 39 against 35.
+  b->staged = prm.precision != WCC_FP64;
   b->inst.resize(B);
   for (int i = 0; i < B; ++i) {
     BatchInst& in = b->inst[i];
