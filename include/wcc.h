@@ -48,7 +48,8 @@
  * - Ownership: device memory and the HIP stream belong to the caller and are
  *   handed over with wcc_bind / wcc_batch_bind; the library never frees them.
  *   Host buffers stay the caller's; reads and writes copy synchronously on
- *   the bound stream.  wcc_destroy frees host-side state, graphs and the
+ *   the bound stream (states of up to 2 MiB through pinned host memory, of
+ *   which the process keeps at most eight such pieces for later contexts).  wcc_destroy frees host-side state, graphs and the
  *   library's own capture stream.  A context is not thread-safe; separate
  *   contexts are independent.
  * - Stream order: wcc_step and wcc_run only enqueue work; wcc_advance,
@@ -163,8 +164,8 @@ int wcc_run(wcc_ctx* ctx, int64_t half_steps, double cfl);
 
 /* Advance to t_end with CFL time steps (Section 5 preamble; the step that
  * would pass t_end is clipped to it), at most max_half_steps (<= 0:
- * unlimited).  Synchronises at the end of every chunk (a graph, or the one
- * launch of a small mesh) to read the 16-byte status.  *taken (may be NULL)
+ * unlimited).  Synchronises after every few graphs (or the one launch of a
+ * small mesh) to read the status.  *taken (may be NULL)
  * receives the half-steps done by this call.  Errors: WCC_ESTATE, WCC_EINVAL (t_end before the current time),
  * WCC_EDEVICE, WCC_ENONFINITE if a step raised a flag (the state after that
  * step is kept for inspection). */

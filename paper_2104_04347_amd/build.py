@@ -25,7 +25,7 @@ LIB = os.path.join(OUT_DIR, "libwcc.so")
 TIMELINE_LIB = os.path.join(OUT_DIR, "libwcc_timeline.so")
 ROOT = os.path.dirname(HERE)
 
-SOURCES = ["wcc_kernels.hip", "wcc_kernels_wide.hip", "wcc_march.hip", "wcc_ctrl.hip", "wcc_batch.hip", "wcc_api.hip", "wcc2d_kernels.hip", "wcc2d_api.hip"]
+SOURCES = ["wcc_kernels.hip", "wcc_kernels_wide.hip", "wcc_march.hip", "wcc_ctrl.hip", "wcc_host.hip", "wcc_batch.hip", "wcc_api.hip", "wcc2d_kernels.hip", "wcc2d_api.hip"]
 # diagnostic build: kernel translation unit -> its timestamped replacement
 TIMELINE_SOURCES = {"wcc_kernels.hip": "wcc_timeline_1d.hip", "wcc_kernels_wide.hip": "wcc_timeline_1d_wide.hip",
                     "wcc2d_kernels.hip": "wcc_timeline_2d.hip"}

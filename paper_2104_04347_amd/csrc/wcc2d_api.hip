@@ -22,6 +22,7 @@
 #include "wcc2d.h"
 #include "wcc2d_internal.hpp"
 #include "wcc_ctrl.hpp"
+#include "wcc_host.hpp"
 
 using wcc::Ctrl;
 using wcc2d::Step2Args;
@@ -54,8 +55,9 @@ struct wcc2d_ctx {
   hipStream_t capture = nullptr;
   hipGraphExec_t graphs[6] = {};
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  int grid[2] = {0, 0};      // resolved blocks per launch from mesh 0 / 1 (0: not resolved yet)
   std::string err;
-  std::vector<unsigned long long> stage_zero;
+  char* pinned = nullptr;    // staging buffer of small states and status reports (wcc_host.hpp), once needed
 };
 
 namespace {
@@ -119,6 +121,8 @@ Step2Args args_for(const wcc2d_ctx* c, int parity, int slot, double dt_fixed) {
 
 int blocks_for(wcc2d_ctx* c, int parity) {
   if (c->blocks > 0) return c->blocks;
+  // resolved once per shape (the occupancy query costs host time otherwise)
+  if (c->grid[parity] > 0) return c->grid[parity];
   // work units over the new mesh: 8 x 8 tiles (variant 0) or rows of
   // 64-column strips
   const int64_t nx = mesh_nx(c, 1 - parity), ny = mesh_ny(c, 1 - parity);
@@ -130,7 +134,8 @@ int blocks_for(wcc2d_ctx* c, int parity) {
       per_cu < 1)
     per_cu = 1;
   const int64_t full = (int64_t)per_cu * c->cu, need = (units + waves - 1) / waves;
-  return (int)std::max<int64_t>(1, std::min(full, need));
+  c->grid[parity] = (int)std::max<int64_t>(1, std::min(full, need));
+  return c->grid[parity];
 }
 
 int enqueue2(wcc2d_ctx* c, int parity, int slot, double dt_fixed, hipStream_t s) {
@@ -178,7 +183,44 @@ int set_fields(wcc2d_ctx* c, double t_end, double cfl) {
   return WCC_OK;
 }
 
+char* pinned_of(wcc2d_ctx* c) {
+  if (!c->pinned) c->pinned = wcc::stage_acquire();
+  return c->pinned;
+}
+
+int64_t cells_of(const wcc2d_ctx* c, int parity) { return mesh_nx(c, parity) * mesh_ny(c, parity); }
+
+// The state's planes on mesh `parity` as rows.
+wcc::Rows<double> rows_of(const wcc2d_ctx* c, int parity) {
+  wcc::Rows<double> r{};
+  r.p = c->q[parity];
+  r.ld = c->plane;
+  r.nc = c->nc * c->nd;
+  r.P = 0;
+  r.n = (int32_t)cells_of(c, parity);
+  return r;
+}
+
+// Half-steps wcc2d_advance enqueues before it looks again: as in 1D
+// (wcc_api.hip), dt = cfl / smax.
+int64_t chunk_for2(const Ctrl& h, int64_t launched, double t_end, double cfl) {
+  const int s = (int)(launched % 3);
+  double smax;
+  std::memcpy(&smax, &h.smax[s], 8);
+  const double est = (t_end - h.t[s]) / (cfl / smax);
+  if (!(est >= 0.0)) return kChunk2;
+  if (est + 1.0 < (double)kChunk2) return (int64_t)est + 2;
+  return kChunk2 * std::max<int64_t>(1, std::min<int64_t>(4, (int64_t)(std::min(est, 1e6) / kChunk2)));
+}
+
 int read_ctrl2(wcc2d_ctx* c, Ctrl* h) {
+  if (char* st = pinned_of(c)) {
+    HIPCHK2(c, wcc::launch_report(c->ctrl, c->parts, st, c->stream));
+    HIPCHK2(c, hipStreamSynchronize(c->stream));
+    std::memcpy(h, st, sizeof *h);
+    c->steps = h->steps_done;
+    return WCC_OK;
+  }
   std::vector<unsigned long long> parts(wcc::kSmaxPartsBytes / sizeof(unsigned long long));
   HIPCHK2(c, hipMemcpyAsync(h, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream));
   HIPCHK2(c, hipMemcpyAsync(parts.data(), c->parts, wcc::kSmaxPartsBytes, hipMemcpyDeviceToHost, c->stream));
@@ -314,17 +356,19 @@ int wcc2d_write_dofs(wcc2d_ctx* c, const double* host, int parity, double t) {
   if (!c) return WCC_EINVAL;
   if (!c->bound) return fail2(c, WCC_ESTATE, "wcc2d_write_dofs before wcc2d_bind");
   if (!host || (parity != 0 && parity != 1) || !std::isfinite(t)) return fail2(c, WCC_EINVAL, "bad arguments");
-  const size_t cells = (size_t)(mesh_nx(c, parity) * mesh_ny(c, parity));
-  for (int r = 0; r < c->nc * c->nd; ++r)
-    HIPCHK2(c, hipMemcpyAsync(c->q[parity] + (size_t)r * c->plane, host + (size_t)r * cells, cells * 8,
-                              hipMemcpyHostToDevice, c->stream));
-  Ctrl h;
-  std::memset(&h, 0, sizeof h);
-  h.t[0] = h.t[1] = h.t[2] = t;
-  h.t_end = std::numeric_limits<double>::infinity();
-  HIPCHK2(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, c->stream));
-  c->stage_zero.assign(wcc::kSmaxPartsBytes / sizeof(unsigned long long), 0ull);
-  HIPCHK2(c, hipMemcpyAsync(c->parts, c->stage_zero.data(), wcc::kSmaxPartsBytes, hipMemcpyHostToDevice, c->stream));
+  const size_t cells = (size_t)cells_of(c, parity);
+  const int rows = c->nc * c->nd;
+  if (wcc::stage_fits(rows, 0, (int64_t)cells) && pinned_of(c)) {
+    std::memcpy(c->pinned + wcc::kStageHead, host, (size_t)rows * cells * 8);
+    HIPCHK2(c, wcc::launch_rows_in<double>(rows_of(c, parity), c->pinned, c->stream));
+  } else {
+    for (int r = 0; r < rows; ++r)
+      HIPCHK2(c, hipMemcpyAsync(c->q[parity] + (size_t)r * c->plane, host + (size_t)r * cells, cells * 8,
+                                hipMemcpyHostToDevice, c->stream));
+  }
+  wcc::RingInit init{};
+  init.t = t;
+  HIPCHK2(c, wcc::launch_init_ring(c->ctrl, c->parts, init, c->stream));
   const int blocks = (int)std::min<int64_t>((int64_t)(cells + 255) / 256, 4LL * c->cu);
   hipError_t e = wcc2d::launch_state_speed2(args_for(c, parity, 0, 0.0), c->eq, c->P, blocks, c->stream);
   if (e != hipSuccess) return fail2(c, WCC_EDEVICE, "speed kernel: %s", hipGetErrorString(e));
@@ -384,8 +428,7 @@ int wcc2d_advance(wcc2d_ctx* c, double t_end, double cfl, int64_t max_half_steps
   while (true) {
     const int64_t done = c->steps - start;
     if (done >= cap) break;
-    const int64_t want = std::min<int64_t>(cap - done, kChunk2);
-    rc = run2(c, want, false);
+    rc = run2(c, std::min<int64_t>(cap - done, chunk_for2(h, c->launched, t_end, cfl)), false);
     if (rc) return rc;
     rc = read_ctrl2(c, &h);
     if (rc) return rc;
@@ -403,14 +446,25 @@ int wcc2d_advance(wcc2d_ctx* c, double t_end, double cfl, int64_t max_half_steps
 int wcc2d_read_dofs(wcc2d_ctx* c, double* host, int64_t cap, wcc2d_state_info* info) {
   if (!c) return WCC_EINVAL;
   if (!c->bound || !c->written) return fail2(c, WCC_ESTATE, "no state written");
+  // a small state comes with the status in one synchronisation: from the mesh
+  // it should be on, and again if half-steps turn out not to have been taken
+  const int rows = c->nc * c->nd, guess = parity_now(c);
+  const bool small = host && wcc::stage_fits(rows, 0, c->plane) && pinned_of(c);
+  if (small) HIPCHK2(c, wcc::launch_rows_out<double>(rows_of(c, guess), c->pinned, c->stream));
   Ctrl h;
   int rc = read_ctrl2(c, &h);
   if (rc) return rc;
   const int parity = parity_now(c);
-  const size_t cells = (size_t)(mesh_nx(c, parity) * mesh_ny(c, parity));
-  if (host) {
-    if (cap < (int64_t)(c->nc * c->nd * cells)) return fail2(c, WCC_ESIZE, "host buffer too small");
-    for (int r = 0; r < c->nc * c->nd; ++r)
+  const size_t cells = (size_t)cells_of(c, parity);
+  if (host && cap < (int64_t)(rows * cells)) return fail2(c, WCC_ESIZE, "host buffer too small");
+  if (small) {
+    if (parity != guess) {
+      HIPCHK2(c, wcc::launch_rows_out<double>(rows_of(c, parity), c->pinned, c->stream));
+      HIPCHK2(c, hipStreamSynchronize(c->stream));
+    }
+    std::memcpy(host, c->pinned + wcc::kStageHead, (size_t)rows * cells * 8);
+  } else if (host) {
+    for (int r = 0; r < rows; ++r)
       HIPCHK2(c, hipMemcpyAsync(host + (size_t)r * cells, c->q[parity] + (size_t)r * c->plane, cells * 8,
                                 hipMemcpyDeviceToHost, c->stream));
     HIPCHK2(c, hipStreamSynchronize(c->stream));
@@ -483,6 +537,7 @@ int wcc2d_set_launch(wcc2d_ctx* c, int threads_per_block, int blocks, int varian
   c->threads = threads_per_block ? threads_per_block : 256;
   c->blocks = blocks;
   if (variant >= 0) c->variant = variant;
+  c->grid[0] = c->grid[1] = 0;
   drop_graphs(c);
   return WCC_OK;
 }
@@ -505,6 +560,7 @@ void wcc2d_destroy(wcc2d_ctx* c) {
   if (c->capture) (void)hipStreamDestroy(c->capture);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
+  wcc::stage_release(c->pinned);
   delete c;
 }
 

@@ -24,6 +24,7 @@
 #include "wcc.h"
 #include "wcc_internal.hpp"
 #include "wcc_ctrl.hpp"
+#include "wcc_host.hpp"
 #include "wcc_march.hpp"
 #include "wcc_wide.hpp"
 
@@ -77,7 +78,7 @@ struct wcc_ctx {
   double known_t_end = 0.0, known_cfl = 0.0;
   std::string err;
   std::vector<float> stage;
-  std::vector<unsigned long long> stage_zero;
+  char* pinned = nullptr;    // staging buffer of small states and status reports (wcc_host.hpp), once needed
 };
 
 namespace {
@@ -307,10 +308,45 @@ int set_ctrl_fields(wcc_ctx* c, double t_end, double cfl) {
   return WCC_OK;
 }
 
+char* pinned_of(wcc_ctx* c) {
+  if (!c->pinned) c->pinned = wcc::stage_acquire();
+  return c->pinned;
+}
+
+// The derivative and point-value rows of the state on mesh `parity`.
+template <class R>
+wcc::Rows<R> rows_of(const wcc_ctx* c, int parity) {
+  wcc::Rows<R> r{};
+  r.p = c->p[parity];
+  r.d = static_cast<R*>(c->d[parity]);
+  r.ld = c->ld;
+  r.nc = c->nc;
+  r.P = c->P;
+  r.n = (int32_t)ncells_of(c, parity);
+  return r;
+}
+
+// Enqueue the copy of a small state into / out of the staging buffer.
+hipError_t rows_in(wcc_ctx* c, int parity) {
+  return c->prm.precision == WCC_FP64 ? wcc::launch_rows_in<double>(rows_of<double>(c, parity), c->pinned, c->stream)
+                                      : wcc::launch_rows_in<float>(rows_of<float>(c, parity), c->pinned, c->stream);
+}
+hipError_t rows_out(wcc_ctx* c, int parity) {
+  return c->prm.precision == WCC_FP64 ? wcc::launch_rows_out<double>(rows_of<double>(c, parity), c->pinned, c->stream)
+                                      : wcc::launch_rows_out<float>(rows_of<float>(c, parity), c->pinned, c->stream);
+}
+
 // Read the control block (synchronising the stream); smax[slot] of the copy
 // is replaced by the max of the slot's partial entries.
 int read_ctrl(wcc_ctx* c, Ctrl* h) {
   static_assert(wcc::kSmaxPartsBytes % 256 == 0, "parts region size");
+  if (char* st = pinned_of(c)) {
+    HIPCHK(c, wcc::launch_report(c->ctrl, c->parts, st, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    std::memcpy(h, st, sizeof *h);
+    c->steps = h->steps_done;
+    return WCC_OK;
+  }
   std::vector<unsigned long long> parts(wcc::kSmaxPartsBytes / sizeof(unsigned long long));
   HIPCHK(c, hipMemcpyAsync(h, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipMemcpyAsync(parts.data(), c->parts, wcc::kSmaxPartsBytes, hipMemcpyDeviceToHost, c->stream));
@@ -322,6 +358,20 @@ int read_ctrl(wcc_ctx* c, Ctrl* h) {
   }
   c->steps = h->steps_done;
   return WCC_OK;
+}
+
+// Half-steps wcc_advance enqueues before it looks again: as many as the way to
+// t_end takes at the present wave speed, in whole graphs (four at most) or,
+// below one, as single launches and one over for the clipped step.  Launches
+// past t_end do nothing.
+int64_t chunk_for(const Ctrl& h, int64_t launched, double dx, double t_end, double cfl) {
+  const int s = (int)(launched % 3);
+  double smax;
+  std::memcpy(&smax, &h.smax[s], 8);
+  const double est = (t_end - h.t[s]) / (cfl * dx / smax);
+  if (!(est >= 0.0)) return kChunk;                  // no wave speed to go by
+  if (est + 1.0 < (double)kChunk) return (int64_t)est + 2;
+  return kChunk * std::max<int64_t>(1, std::min<int64_t>(4, (int64_t)(std::min(est, 1e6) / kChunk)));
 }
 
 bool check_cfl(double cfl) { return cfl > 0.0 && cfl <= 1.0 && std::isfinite(cfl); }
@@ -528,45 +578,47 @@ int wcc_write_dofs(wcc_ctx* c, const double* host, int64_t n_cells, int parity, 
   if (n_cells != n) return fail(c, WCC_ESIZE, "n_cells %lld, mesh of parity %d has %lld", (long long)n_cells, parity,
                                 (long long)n);
   const int P = c->P, nc = c->nc;
-  // point values
-  for (int cc = 0; cc < nc; ++cc)
-    HIPCHK(c, hipMemcpyAsync(c->p[parity] + (size_t)cc * c->ld, host + (size_t)(cc * (P + 1)) * n, n * 8,
-                             hipMemcpyHostToDevice, c->stream));
-  // derivatives
-  if (P > 0) {
-    char* dbase = static_cast<char*>(c->d[parity]);
-    if (c->prm.precision == WCC_FP64) {
-      for (int cc = 0; cc < nc; ++cc)
-        for (int k = 1; k <= P; ++k)
-          HIPCHK(c, hipMemcpyAsync(dbase + ((size_t)(cc * P + k - 1) * c->ld) * 8,
-                                   host + (size_t)(cc * (P + 1) + k) * n, n * 8, hipMemcpyHostToDevice, c->stream));
-    } else {
-      c->stage.resize((size_t)nc * P * n);
-      for (int cc = 0; cc < nc; ++cc)
-        for (int k = 1; k <= P; ++k) {
-          const double* src = host + (size_t)(cc * (P + 1) + k) * n;
-          float* dst = c->stage.data() + (size_t)(cc * P + k - 1) * n;
-          for (int64_t j = 0; j < n; ++j) dst[j] = (float)src[j];
-        }
-      for (int r = 0; r < nc * P; ++r)
-        HIPCHK(c, hipMemcpyAsync(dbase + ((size_t)r * c->ld) * 4, c->stage.data() + (size_t)r * n, n * 4,
-                                 hipMemcpyHostToDevice, c->stream));
+  if (wcc::stage_fits(nc, P, n) && pinned_of(c)) {
+    // (the stream is idle past the previous use: every use of the staging
+    // buffer ends with a synchronisation)
+    std::memcpy(c->pinned + wcc::kStageHead, host, (size_t)(nc * (P + 1) * n) * 8);
+    HIPCHK(c, rows_in(c, parity));
+  } else {
+    // point values
+    for (int cc = 0; cc < nc; ++cc)
+      HIPCHK(c, hipMemcpyAsync(c->p[parity] + (size_t)cc * c->ld, host + (size_t)(cc * (P + 1)) * n, n * 8,
+                               hipMemcpyHostToDevice, c->stream));
+    // derivatives
+    if (P > 0) {
+      char* dbase = static_cast<char*>(c->d[parity]);
+      if (c->prm.precision == WCC_FP64) {
+        for (int cc = 0; cc < nc; ++cc)
+          for (int k = 1; k <= P; ++k)
+            HIPCHK(c, hipMemcpyAsync(dbase + ((size_t)(cc * P + k - 1) * c->ld) * 8,
+                                     host + (size_t)(cc * (P + 1) + k) * n, n * 8, hipMemcpyHostToDevice, c->stream));
+      } else {
+        c->stage.resize((size_t)nc * P * n);
+        for (int cc = 0; cc < nc; ++cc)
+          for (int k = 1; k <= P; ++k) {
+            const double* src = host + (size_t)(cc * (P + 1) + k) * n;
+            float* dst = c->stage.data() + (size_t)(cc * P + k - 1) * n;
+            for (int64_t j = 0; j < n; ++j) dst[j] = (float)src[j];
+          }
+        for (int r = 0; r < nc * P; ++r)
+          HIPCHK(c, hipMemcpyAsync(dbase + ((size_t)r * c->ld) * 4, c->stage.data() + (size_t)r * n, n * 4,
+                                   hipMemcpyHostToDevice, c->stream));
+      }
     }
   }
-  // control block: time in slot 0, everything else cleared
-  Ctrl h;
-  std::memset(&h, 0, sizeof h);
-  h.t[0] = h.t[1] = h.t[2] = t;
-  h.t_end = std::numeric_limits<double>::infinity();
-  h.cfl = 0.0;
+  // control block: time in every slot, everything else cleared
+  wcc::RingInit init{};
+  init.t = t;
   for (int i = 0; i < 3; ++i) {
-    h.ghost[0][i] = c->prm.left_state[i];
-    h.ghost[1][i] = c->prm.right_state[i];
+    init.ghost[0][i] = c->prm.left_state[i];
+    init.ghost[1][i] = c->prm.right_state[i];
   }
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, wcc::launch_init_ring(c->ctrl, c->parts, init, c->stream));
   c->fields_known = false;
-  c->stage_zero.assign(wcc::kSmaxPartsBytes / sizeof(unsigned long long), 0ull);
-  HIPCHK(c, hipMemcpyAsync(c->parts, c->stage_zero.data(), wcc::kSmaxPartsBytes, hipMemcpyHostToDevice, c->stream));
   // wave speed of the written state into slot 0
   hipError_t e;
   const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4LL * c->cu);
@@ -699,7 +751,8 @@ int wcc_advance(wcc_ctx* c, double t_end, double cfl, int64_t max_half_steps, in
   while (true) {
     const int64_t done = c->steps - start;
     if (done >= cap) break;
-    rc = run_chunks(c, std::min<int64_t>(cap - done, marches(c) ? wcc::kMarchSteps : kChunk), false);
+    const int64_t want = marches(c) ? wcc::kMarchSteps : chunk_for(h, c->launched, dx_of(c), t_end, cfl);
+    rc = run_chunks(c, std::min<int64_t>(cap - done, want), false);
     if (rc) return rc;
     rc = read_ctrl(c, &h);  // sets c->steps from the device
     if (rc) return rc;
@@ -717,14 +770,26 @@ int wcc_advance(wcc_ctx* c, double t_end, double cfl, int64_t max_half_steps, in
 int wcc_read_dofs(wcc_ctx* c, double* host, int64_t cap, wcc_state_info* info) {
   if (!c) return WCC_EINVAL;
   if (!c->bound || !c->written) return fail(c, WCC_ESTATE, "no state written");
+  const int P = c->P, nc = c->nc;
+  // a small state comes with the status in one synchronisation: from the mesh
+  // it should be on, and again if half-steps turn out not to have been taken
+  const int64_t most = std::max(ncells_of(c, 0), ncells_of(c, 1));
+  const bool small = host && wcc::stage_fits(nc, P, most) && pinned_of(c);
+  const int guess = current_parity(c);
+  if (small) HIPCHK(c, rows_out(c, guess));
   Ctrl h;
   int rc = read_ctrl(c, &h);
   if (rc) return rc;
   const int parity = current_parity(c);
   const int64_t n = ncells_of(c, parity);
-  const int P = c->P, nc = c->nc;
-  if (host) {
-    if (cap < (int64_t)nc * (P + 1) * n) return fail(c, WCC_ESIZE, "host buffer too small");
+  if (host && cap < (int64_t)nc * (P + 1) * n) return fail(c, WCC_ESIZE, "host buffer too small");
+  if (small) {
+    if (parity != guess) {
+      HIPCHK(c, rows_out(c, parity));
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+    }
+    std::memcpy(host, c->pinned + wcc::kStageHead, (size_t)(nc * (P + 1) * n) * 8);
+  } else if (host) {
     for (int cc = 0; cc < nc; ++cc)
       HIPCHK(c, hipMemcpyAsync(host + (size_t)(cc * (P + 1)) * n, c->p[parity] + (size_t)cc * c->ld, n * 8,
                                hipMemcpyDeviceToHost, c->stream));
@@ -841,6 +906,7 @@ void wcc_destroy(wcc_ctx* c) {
   if (c->capture) (void)hipStreamDestroy(c->capture);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
+  wcc::stage_release(c->pinned);
   delete c;
 }
 
