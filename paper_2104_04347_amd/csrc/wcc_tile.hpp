@@ -142,10 +142,13 @@ __device__ __forceinline__ bool step_time(const StepIn& in, Ctrl* ctrl, unsigned
 
 // Per-block reduction of the wave speeds and flags, then one atomic each into
 // the next slot.  With `parts` the block's atomic goes to entry (block index
-// mod 64).  In launches of up to 64 blocks every block has an entry to itself
-// and raises it at once, without waiting for an answer; in larger ones a look
-// at the stored maximum first lets most blocks skip the atomic, which would
-// queue at its entry (768 blocks: 0.7% of a launch of 48 us).
+// mod 64) and waits for no answer: a look at the stored maximum first, to skip
+// the atomic, kept every block for one more trip to memory at the launch's
+// end, which cost more than the atomics' queueing at their entries at every
+// grid measured (us a half-step with the look and without: Burgers N = 20,000,
+// 80 blocks, 4.45 and 4.09; 100,000, 397 blocks, 5.5 and 4.9; Euler 300,000
+// mixed, 1,191 blocks, 11.9 and 11.4; 2^20, 768 blocks, 42.2 and 41.9).
+// Without `parts` all blocks share one address, and the look stays.
 __device__ __forceinline__ void publish(Ctrl* ctrl, unsigned long long* parts, int slot, double smax,
                                         unsigned flags) {
   __shared__ double red_s[4];
@@ -172,7 +175,7 @@ __device__ __forceinline__ void publish(Ctrl* ctrl, unsigned long long* parts, i
     const unsigned long long bits = (unsigned long long)__double_as_longlong(smax);
     unsigned long long* dst =
         parts ? &parts[(s1 * kSmaxParts + (int)(blockIdx.x % kSmaxParts)) * kSmaxStride] : &ctrl->smax[s1];
-    if (gridDim.x <= kSmaxParts || bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    if (parts || bits > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
       (void)__hip_atomic_fetch_max(dst, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (flags) (void)__hip_atomic_fetch_or(&ctrl->flags[s1], flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
