@@ -57,20 +57,29 @@ void stage_release(char* stage) {
   (void)hipHostFree(stage);
 }
 
+// Largest of the wave's entries as unsigned integers, the order in which the
+// kernels' atomics raised them: a NaN is above every number (wave_max passes
+// NaNs over).
+__device__ __forceinline__ unsigned long long wave_max_bits(unsigned long long e) {
+  const unsigned long long nan = __ballot(e > 0x7ff0000000000000ull);
+  const double top = wave_max(__longlong_as_double((long long)e));
+  if (nan == 0) return (unsigned long long)__double_as_longlong(top);
+  return __shfl(e, __ffsll((long long)nan) - 1);
+}
+
 __global__ __launch_bounds__(64) void k_report(const Ctrl* ctrl, const unsigned long long* parts, Ctrl* out) {
   const int lane = threadIdx.x;
   constexpr int words = (int)(sizeof(Ctrl) / sizeof(unsigned long long));
   static_assert(words <= 64, "one word a lane");
-  double top[3];
+  unsigned long long top[3];
 #pragma unroll
-  for (int s = 0; s < 3; ++s)
-    top[s] = wave_max(__longlong_as_double((long long)parts[(s * kSmaxParts + lane) * kSmaxStride]));
+  for (int s = 0; s < 3; ++s) top[s] = wave_max_bits(parts[(s * kSmaxParts + lane) * kSmaxStride]);
   if (lane < words) {
     constexpr int first = (int)(offsetof(Ctrl, smax) / sizeof(unsigned long long));
     unsigned long long w = reinterpret_cast<const unsigned long long*>(ctrl)[lane];
 #pragma unroll
     for (int s = 0; s < 3; ++s)
-      if (lane == first + s) w = (unsigned long long)__double_as_longlong(top[s]);
+      if (lane == first + s) w = top[s];
     reinterpret_cast<unsigned long long*>(out)[lane] = w;
   }
 }

@@ -147,8 +147,9 @@ __global__ __launch_bounds__(march_tiles(EQ, P, sizeof(R)) * 64) void k_march(co
   }
   if (tile == 0) {
     const int s1 = (a.slot + a.steps) % 3, s2 = s1 == 2 ? 0 : s1 + 1;
+    // (no half-step taken: the slot's entries move on as they are)
     a.parts[(s1 * kSmaxParts + lane) * kSmaxStride] =
-        lane == 0 ? (unsigned long long)__double_as_longlong(smax) : 0ull;
+        taken == 0 ? ring.smax : (lane == 0 ? (unsigned long long)__double_as_longlong(smax) : 0ull);
     a.parts[(s2 * kSmaxParts + lane) * kSmaxStride] = 0ull;
     if (lane == 0) {
       a.ctrl->t[s1] = t;
