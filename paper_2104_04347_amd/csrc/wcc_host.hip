@@ -57,23 +57,27 @@ void stage_release(char* stage) {
   (void)hipHostFree(stage);
 }
 
-// Largest of the wave's entries as unsigned integers, the order in which the
-// kernels' atomics raised them: a NaN is above every number (wave_max passes
-// NaNs over).
-__device__ __forceinline__ unsigned long long wave_max_bits(unsigned long long e) {
-  const unsigned long long nan = __ballot(e > 0x7ff0000000000000ull);
-  const double top = wave_max(__longlong_as_double((long long)e));
-  if (nan == 0) return (unsigned long long)__double_as_longlong(top);
-  return __shfl(e, __ffsll((long long)nan) - 1);
-}
-
 __global__ __launch_bounds__(64) void k_report(const Ctrl* ctrl, const unsigned long long* parts, Ctrl* out) {
   const int lane = threadIdx.x;
   constexpr int words = (int)(sizeof(Ctrl) / sizeof(unsigned long long));
   static_assert(words <= 64, "one word a lane");
-  unsigned long long top[3];
+  // The entries' largest as unsigned integers, the order in which the kernels'
+  // atomics raised them: a NaN is above every number (wave_max passes NaNs over).
+  unsigned long long e[3], top[3];
+  bool nan = false;
 #pragma unroll
-  for (int s = 0; s < 3; ++s) top[s] = wave_max_bits(parts[(s * kSmaxParts + lane) * kSmaxStride]);
+  for (int s = 0; s < 3; ++s) {
+    e[s] = parts[(s * kSmaxParts + lane) * kSmaxStride];
+    nan |= e[s] > 0x7ff0000000000000ull;
+    top[s] = (unsigned long long)__double_as_longlong(wave_max(__longlong_as_double((long long)e[s])));
+  }
+  if (__ballot(nan) != 0) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const unsigned long long who = __ballot(e[s] > 0x7ff0000000000000ull);
+      if (who != 0) top[s] = __shfl(e[s], __ffsll((long long)who) - 1);
+    }
+  }
   if (lane < words) {
     constexpr int first = (int)(offsetof(Ctrl, smax) / sizeof(unsigned long long));
     unsigned long long w = reinterpret_cast<const unsigned long long*>(ctrl)[lane];
