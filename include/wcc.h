@@ -48,10 +48,11 @@
  * - Ownership: device memory and the HIP stream belong to the caller and are
  *   handed over with wcc_bind / wcc_batch_bind; the library never frees them.
  *   Host buffers stay the caller's; reads and writes copy synchronously on
- *   the bound stream (states of up to 2 MiB through pinned host memory, of
- *   which the process keeps at most eight such pieces for later contexts).
- *   wcc_destroy frees host-side state, graphs and the library's own capture
- *   stream.  A context is not thread-safe; separate contexts are independent.
+ *   the bound stream.  States of up to 2 MiB and status reports go through a
+ *   2 MiB piece of pinned host memory, held for the length of the call; the
+ *   process keeps at most eight such pieces for later calls.  wcc_destroy
+ *   frees host-side state, graphs and the library's own capture stream.  A
+ *   context is not thread-safe; separate contexts are independent.
  * - Stream order: wcc_step and wcc_run only enqueue work; wcc_advance,
  *   wcc_read_dofs, wcc_write_dofs and wcc_totals synchronise the bound
  *   stream.

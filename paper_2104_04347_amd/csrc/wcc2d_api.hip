@@ -57,7 +57,6 @@ struct wcc2d_ctx {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   int grid[2] = {0, 0};      // resolved blocks per launch from mesh 0 / 1 (0: not resolved yet)
   std::string err;
-  char* pinned = nullptr;    // staging buffer of small states and status reports (wcc_host.hpp), once needed
 };
 
 namespace {
@@ -187,11 +186,6 @@ int set_fields(wcc2d_ctx* c, double t_end, double cfl) {
   return WCC_OK;
 }
 
-char* pinned_of(wcc2d_ctx* c) {
-  if (!c->pinned) c->pinned = wcc::stage_acquire();
-  return c->pinned;
-}
-
 int64_t cells_of(const wcc2d_ctx* c, int parity) { return mesh_nx(c, parity) * mesh_ny(c, parity); }
 
 // The state's planes on mesh `parity` as rows.
@@ -217,10 +211,12 @@ int64_t chunk_for2(const Ctrl& h, int64_t launched, double t_end, double cfl) {
   return kChunk2 * std::max<int64_t>(1, std::min<int64_t>(4, (int64_t)(std::min(est, 1e6) / kChunk2)));
 }
 
-int read_ctrl2(wcc2d_ctx* c, Ctrl* h) {
-  if (char* st = pinned_of(c)) {
+int read_ctrl2(wcc2d_ctx* c, Ctrl* h, wcc::StageLoan& loan) {
+  if (char* st = loan.get()) {
+    loan.enqueued();
     HIPCHK2(c, wcc::launch_report(c->ctrl, c->parts, st, c->stream));
     HIPCHK2(c, hipStreamSynchronize(c->stream));
+    loan.waited();
     std::memcpy(h, st, sizeof *h);
     c->steps = h->steps_done;
     return WCC_OK;
@@ -362,9 +358,11 @@ int wcc2d_write_dofs(wcc2d_ctx* c, const double* host, int parity, double t) {
   if (!host || (parity != 0 && parity != 1) || !std::isfinite(t)) return fail2(c, WCC_EINVAL, "bad arguments");
   const size_t cells = (size_t)cells_of(c, parity);
   const int rows = c->nc * c->nd;
-  if (wcc::stage_fits(rows, 0, (int64_t)cells) && pinned_of(c)) {
-    std::memcpy(c->pinned + wcc::kStageHead, host, (size_t)rows * cells * 8);
-    HIPCHK2(c, wcc::launch_rows_in<double>(rows_of(c, parity), c->pinned, c->stream));
+  wcc::StageLoan loan(c->stream);
+  if (wcc::stage_fits(rows, 0, (int64_t)cells) && loan.get()) {
+    std::memcpy(loan.get() + wcc::kStageHead, host, (size_t)rows * cells * 8);
+    loan.enqueued();
+    HIPCHK2(c, wcc::launch_rows_in<double>(rows_of(c, parity), loan.get(), c->stream));
   } else {
     for (int r = 0; r < rows; ++r)
       HIPCHK2(c, hipMemcpyAsync(c->q[parity] + (size_t)r * c->plane, host + (size_t)r * cells, cells * 8,
@@ -377,7 +375,7 @@ int wcc2d_write_dofs(wcc2d_ctx* c, const double* host, int parity, double t) {
   hipError_t e = wcc2d::launch_state_speed2(args_for(c, parity, 0, 0.0), c->eq, c->P, blocks, c->stream);
   if (e != hipSuccess) return fail2(c, WCC_EDEVICE, "speed kernel: %s", hipGetErrorString(e));
   Ctrl back;
-  const int rc = read_ctrl2(c, &back);
+  const int rc = read_ctrl2(c, &back, loan);
   if (rc) return rc;
   c->written = true;
   c->parity_w = parity;
@@ -419,8 +417,9 @@ int wcc2d_advance(wcc2d_ctx* c, double t_end, double cfl, int64_t max_half_steps
   if (!c) return WCC_EINVAL;
   if (!c->bound || !c->written) return fail2(c, WCC_ESTATE, "no state written");
   if (!cfl_ok(cfl) || !std::isfinite(t_end)) return fail2(c, WCC_EINVAL, "bad cfl or t_end");
+  wcc::StageLoan loan(c->stream);
   Ctrl h;
-  int rc = read_ctrl2(c, &h);
+  int rc = read_ctrl2(c, &h, loan);
   if (rc) return rc;
   const int s0 = (int)(c->launched % 3);
   if (t_end < h.t[s0]) return fail2(c, WCC_EINVAL, "t_end %g before the current time %g", t_end, h.t[s0]);
@@ -434,7 +433,7 @@ int wcc2d_advance(wcc2d_ctx* c, double t_end, double cfl, int64_t max_half_steps
     if (done >= cap) break;
     rc = run2(c, std::min<int64_t>(cap - done, chunk_for2(h, c->launched, t_end, cfl)), false);
     if (rc) return rc;
-    rc = read_ctrl2(c, &h);
+    rc = read_ctrl2(c, &h, loan);
     if (rc) return rc;
     const int s = (int)(c->launched % 3);
     if (h.flags[s]) {
@@ -453,20 +452,26 @@ int wcc2d_read_dofs(wcc2d_ctx* c, double* host, int64_t cap, wcc2d_state_info* i
   // a small state comes with the status in one synchronisation: from the mesh
   // it should be on, and again if half-steps turn out not to have been taken
   const int rows = c->nc * c->nd, guess = parity_now(c);
-  const bool small = host && wcc::stage_fits(rows, 0, c->plane) && pinned_of(c);
-  if (small) HIPCHK2(c, wcc::launch_rows_out<double>(rows_of(c, guess), c->pinned, c->stream));
+  wcc::StageLoan loan(c->stream);
+  const bool small = host && wcc::stage_fits(rows, 0, c->plane) && loan.get();
+  if (small) {
+    loan.enqueued();
+    HIPCHK2(c, wcc::launch_rows_out<double>(rows_of(c, guess), loan.get(), c->stream));
+  }
   Ctrl h;
-  int rc = read_ctrl2(c, &h);
+  int rc = read_ctrl2(c, &h, loan);
   if (rc) return rc;
   const int parity = parity_now(c);
   const size_t cells = (size_t)cells_of(c, parity);
   if (host && cap < (int64_t)(rows * cells)) return fail2(c, WCC_ESIZE, "host buffer too small");
   if (small) {
     if (parity != guess) {
-      HIPCHK2(c, wcc::launch_rows_out<double>(rows_of(c, parity), c->pinned, c->stream));
+      loan.enqueued();
+      HIPCHK2(c, wcc::launch_rows_out<double>(rows_of(c, parity), loan.get(), c->stream));
       HIPCHK2(c, hipStreamSynchronize(c->stream));
+      loan.waited();
     }
-    std::memcpy(host, c->pinned + wcc::kStageHead, (size_t)rows * cells * 8);
+    std::memcpy(host, loan.get() + wcc::kStageHead, (size_t)rows * cells * 8);
   } else if (host) {
     for (int r = 0; r < rows; ++r)
       HIPCHK2(c, hipMemcpyAsync(host + (size_t)r * cells, c->q[parity] + (size_t)r * c->plane, cells * 8,
@@ -564,7 +569,6 @@ void wcc2d_destroy(wcc2d_ctx* c) {
   if (c->capture) (void)hipStreamDestroy(c->capture);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
-  wcc::stage_release(c->pinned);
   delete c;
 }
 

@@ -78,7 +78,6 @@ struct wcc_ctx {
   double known_t_end = 0.0, known_cfl = 0.0;
   std::string err;
   std::vector<float> stage;
-  char* pinned = nullptr;    // staging buffer of small states and status reports (wcc_host.hpp), once needed
 };
 
 namespace {
@@ -308,11 +307,6 @@ int set_ctrl_fields(wcc_ctx* c, double t_end, double cfl) {
   return WCC_OK;
 }
 
-char* pinned_of(wcc_ctx* c) {
-  if (!c->pinned) c->pinned = wcc::stage_acquire();
-  return c->pinned;
-}
-
 // The derivative and point-value rows of the state on mesh `parity`.
 template <class R>
 wcc::Rows<R> rows_of(const wcc_ctx* c, int parity) {
@@ -327,22 +321,26 @@ wcc::Rows<R> rows_of(const wcc_ctx* c, int parity) {
 }
 
 // Enqueue the copy of a small state into / out of the staging buffer.
-hipError_t rows_in(wcc_ctx* c, int parity) {
-  return c->prm.precision == WCC_FP64 ? wcc::launch_rows_in<double>(rows_of<double>(c, parity), c->pinned, c->stream)
-                                      : wcc::launch_rows_in<float>(rows_of<float>(c, parity), c->pinned, c->stream);
+hipError_t rows_in(wcc_ctx* c, int parity, wcc::StageLoan& loan) {
+  loan.enqueued();
+  return c->prm.precision == WCC_FP64 ? wcc::launch_rows_in<double>(rows_of<double>(c, parity), loan.get(), c->stream)
+                                      : wcc::launch_rows_in<float>(rows_of<float>(c, parity), loan.get(), c->stream);
 }
-hipError_t rows_out(wcc_ctx* c, int parity) {
-  return c->prm.precision == WCC_FP64 ? wcc::launch_rows_out<double>(rows_of<double>(c, parity), c->pinned, c->stream)
-                                      : wcc::launch_rows_out<float>(rows_of<float>(c, parity), c->pinned, c->stream);
+hipError_t rows_out(wcc_ctx* c, int parity, wcc::StageLoan& loan) {
+  loan.enqueued();
+  return c->prm.precision == WCC_FP64 ? wcc::launch_rows_out<double>(rows_of<double>(c, parity), loan.get(), c->stream)
+                                      : wcc::launch_rows_out<float>(rows_of<float>(c, parity), loan.get(), c->stream);
 }
 
 // Read the control block (synchronising the stream); smax[slot] of the copy
 // is replaced by the max of the slot's partial entries.
-int read_ctrl(wcc_ctx* c, Ctrl* h) {
+int read_ctrl(wcc_ctx* c, Ctrl* h, wcc::StageLoan& loan) {
   static_assert(wcc::kSmaxPartsBytes % 256 == 0, "parts region size");
-  if (char* st = pinned_of(c)) {
+  if (char* st = loan.get()) {
+    loan.enqueued();
     HIPCHK(c, wcc::launch_report(c->ctrl, c->parts, st, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    loan.waited();
     std::memcpy(h, st, sizeof *h);
     c->steps = h->steps_done;
     return WCC_OK;
@@ -578,11 +576,10 @@ int wcc_write_dofs(wcc_ctx* c, const double* host, int64_t n_cells, int parity, 
   if (n_cells != n) return fail(c, WCC_ESIZE, "n_cells %lld, mesh of parity %d has %lld", (long long)n_cells, parity,
                                 (long long)n);
   const int P = c->P, nc = c->nc;
-  if (wcc::stage_fits(nc, P, n) && pinned_of(c)) {
-    // (the stream is idle past the previous use: every use of the staging
-    // buffer ends with a synchronisation)
-    std::memcpy(c->pinned + wcc::kStageHead, host, (size_t)(nc * (P + 1) * n) * 8);
-    HIPCHK(c, rows_in(c, parity));
+  wcc::StageLoan loan(c->stream);
+  if (wcc::stage_fits(nc, P, n) && loan.get()) {
+    std::memcpy(loan.get() + wcc::kStageHead, host, (size_t)(nc * (P + 1) * n) * 8);
+    HIPCHK(c, rows_in(c, parity, loan));
   } else {
     // point values
     for (int cc = 0; cc < nc; ++cc)
@@ -633,7 +630,7 @@ int wcc_write_dofs(wcc_ctx* c, const double* host, int64_t n_cells, int parity, 
   }
   if (e != hipSuccess) return fail(c, WCC_EDEVICE, "speed kernel: %s", hipGetErrorString(e));
   Ctrl back;
-  int rc0 = read_ctrl(c, &back);
+  int rc0 = read_ctrl(c, &back, loan);
   if (rc0) return rc0;
   c->written = true;
   c->parity_w = parity;
@@ -738,8 +735,9 @@ int wcc_advance(wcc_ctx* c, double t_end, double cfl, int64_t max_half_steps, in
   if (!c) return WCC_EINVAL;
   if (!c->bound || !c->written) return fail(c, WCC_ESTATE, "no state written");
   if (!check_cfl(cfl) || !std::isfinite(t_end)) return fail(c, WCC_EINVAL, "bad cfl or t_end");
+  wcc::StageLoan loan(c->stream);
   Ctrl h;
-  int rc = read_ctrl(c, &h);
+  int rc = read_ctrl(c, &h, loan);
   if (rc) return rc;
   const int s0 = (int)(c->launched % 3);
   if (t_end < h.t[s0]) return fail(c, WCC_EINVAL, "t_end %g before the current time %g", t_end, h.t[s0]);
@@ -754,7 +752,7 @@ int wcc_advance(wcc_ctx* c, double t_end, double cfl, int64_t max_half_steps, in
     const int64_t want = marches(c) ? wcc::kMarchSteps : chunk_for(h, c->launched, dx_of(c), t_end, cfl);
     rc = run_chunks(c, std::min<int64_t>(cap - done, want), false);
     if (rc) return rc;
-    rc = read_ctrl(c, &h);  // sets c->steps from the device
+    rc = read_ctrl(c, &h, loan);  // sets c->steps from the device
     if (rc) return rc;
     const int s = (int)(c->launched % 3);
     if (h.flags[s]) {
@@ -774,21 +772,23 @@ int wcc_read_dofs(wcc_ctx* c, double* host, int64_t cap, wcc_state_info* info) {
   // a small state comes with the status in one synchronisation: from the mesh
   // it should be on, and again if half-steps turn out not to have been taken
   const int64_t most = std::max(ncells_of(c, 0), ncells_of(c, 1));
-  const bool small = host && wcc::stage_fits(nc, P, most) && pinned_of(c);
+  wcc::StageLoan loan(c->stream);
+  const bool small = host && wcc::stage_fits(nc, P, most) && loan.get();
   const int guess = current_parity(c);
-  if (small) HIPCHK(c, rows_out(c, guess));
+  if (small) HIPCHK(c, rows_out(c, guess, loan));
   Ctrl h;
-  int rc = read_ctrl(c, &h);
+  int rc = read_ctrl(c, &h, loan);
   if (rc) return rc;
   const int parity = current_parity(c);
   const int64_t n = ncells_of(c, parity);
   if (host && cap < (int64_t)nc * (P + 1) * n) return fail(c, WCC_ESIZE, "host buffer too small");
   if (small) {
     if (parity != guess) {
-      HIPCHK(c, rows_out(c, parity));
+      HIPCHK(c, rows_out(c, parity, loan));
       HIPCHK(c, hipStreamSynchronize(c->stream));
+      loan.waited();
     }
-    std::memcpy(host, c->pinned + wcc::kStageHead, (size_t)(nc * (P + 1) * n) * 8);
+    std::memcpy(host, loan.get() + wcc::kStageHead, (size_t)(nc * (P + 1) * n) * 8);
   } else if (host) {
     for (int cc = 0; cc < nc; ++cc)
       HIPCHK(c, hipMemcpyAsync(host + (size_t)(cc * (P + 1)) * n, c->p[parity] + (size_t)cc * c->ld, n * 8,
@@ -906,7 +906,6 @@ void wcc_destroy(wcc_ctx* c) {
   if (c->capture) (void)hipStreamDestroy(c->capture);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
-  wcc::stage_release(c->pinned);
   delete c;
 }
 

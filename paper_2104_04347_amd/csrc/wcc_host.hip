@@ -12,7 +12,6 @@
 
 #include <algorithm>
 #include <mutex>
-#include <vector>
 
 #include "wcc_host.hpp"
 #include "wcc_tile.hpp"
@@ -20,41 +19,38 @@
 namespace wcc {
 
 namespace {
-constexpr size_t kKept = 8;
+constexpr int kKept = 8;
+// plain data, never destroyed: usable until the process ends
 std::mutex g_stage_mu;
-std::vector<char*> g_stages;
+char* g_stages[kKept];
+int g_stage_n = 0;
 }  // namespace
 
-char* stage_acquire() {
+char* StageLoan::get() {
+  if (mem_) return mem_;
   {
     std::lock_guard<std::mutex> lk(g_stage_mu);
-    if (!g_stages.empty()) {
-      char* s = g_stages.back();
-      g_stages.pop_back();
-      return s;
-    }
+    if (g_stage_n > 0) return mem_ = g_stages[--g_stage_n];
   }
   void* s = nullptr;
   if (hipHostMalloc(&s, kStageBytes, hipHostMallocPortable) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
-  return static_cast<char*>(s);
+  return mem_ = static_cast<char*>(s);
 }
 
-void stage_release(char* stage) {
-  if (!stage) return;
+StageLoan::~StageLoan() {
+  if (!mem_) return;
+  if (busy_) (void)hipStreamSynchronize(stream_);
   {
     std::lock_guard<std::mutex> lk(g_stage_mu);
-    if (g_stages.size() < kKept) {
-      try {
-        g_stages.push_back(stage);
-        return;
-      } catch (...) {
-      }
+    if (g_stage_n < kKept) {
+      g_stages[g_stage_n++] = mem_;
+      return;
     }
   }
-  (void)hipHostFree(stage);
+  (void)hipHostFree(mem_);
 }
 
 __global__ __launch_bounds__(64) void k_report(const Ctrl* ctrl, const unsigned long long* parts, Ctrl* out) {

@@ -16,12 +16,30 @@ constexpr size_t kStageBytes = size_t(2) << 20;
 constexpr size_t kStageHead = 1024;
 constexpr size_t kStageRows = kStageBytes - kStageHead;
 
-// A staging buffer of this process, or null where no pinned memory is to be
-// had (the caller then copies directly).  Buffers given back are kept for the
-// next context, eight at most; safe from several threads.  A buffer belongs
-// to one context at a time.
-char* stage_acquire();
-void stage_release(char* stage);
+// A staging buffer on loan from the process for one call that works on
+// `stream`: taken when first needed, given back at the end of the call, so that
+// a context holds none between calls.  A call that ends with work on the buffer
+// still enqueued (an error half way) waits for the stream first.  The process
+// keeps at most eight buffers for later calls and makes another where more
+// calls are at work at once; safe from several threads.
+class StageLoan {
+ public:
+  explicit StageLoan(hipStream_t stream) : stream_(stream) {}
+  ~StageLoan();
+  StageLoan(const StageLoan&) = delete;
+  StageLoan& operator=(const StageLoan&) = delete;
+  // The buffer, or null where no pinned memory is to be had (the caller then
+  // copies directly).
+  char* get();
+  // Work on the buffer has been enqueued / waited for.
+  void enqueued() { busy_ = true; }
+  void waited() { busy_ = false; }
+
+ private:
+  hipStream_t stream_;
+  char* mem_ = nullptr;
+  bool busy_ = false;
+};
 
 // The control block with smax[s] replaced by the largest partial entry of
 // slot s, written to the head of a staging buffer; complete once the stream
