@@ -195,8 +195,11 @@ int wcc_totals(wcc_ctx* ctx, double* per_component);
  * tile per wave (pays when the state does not fit the caches).  Variant 4
  * is the second tile shape: wave tiles of 128 old cells, two per lane (127
  * new cells), direct stores.  -1 keeps the current variant.  At creation the
- * variant is 3 when the two state buffers exceed 512 MiB, else 1.  Used by
- * the autotuner.  Errors: WCC_EINVAL (variant outside -1..4, threads not
+ * variant is 3 when the two state buffers exceed 512 MiB, else 1.  With the
+ * values at creation (256, 0, that variant), set here or not, a mesh of up to
+ * 16 x 63 cells (fewer for Euler from P = 2 on) runs many half-steps in one
+ * launch (wcc_run); any other values choose a launch for each half-step.
+ * Used by the autotuner.  Errors: WCC_EINVAL (variant outside -1..4, threads not
  * 64..256 in steps of 64, negative blocks). */
 int wcc_set_launch(wcc_ctx* ctx, int threads_per_block, int blocks, int variant);
 

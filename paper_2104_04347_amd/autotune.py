@@ -18,7 +18,8 @@ the caller's stream, after a warm-up; the fastest few are then re-timed
 round-robin (`refine`) and the one with the smallest median wins.  The best
 shape is cached in a JSON file
 (``$WCC_AUTOTUNE_CACHE``, default ``~/.cache/wcc_autotune.json``) keyed by
-equation, degree, precision, limiter and a power-of-two size bucket.
+equation, degree, precision, limiter and a power-of-two size bucket, or, for
+the smallest meshes, the size itself.
 """
 from __future__ import annotations
 
@@ -57,8 +58,17 @@ def _save_cache(c: dict) -> None:
         pass
 
 
+# The largest mesh that the default launch shape may run as one launch of many
+# half-steps (16 tiles of 63 cells; fewer for some equations and degrees).
+ONE_LAUNCH_MAX = 16 * 63
+
+
 def key_single(equation: str, P: int, N: int, precision: str, limiter: bool) -> str:
-    return f"single/{equation}/P{P}/{precision}/{'lim' if limiter else 'nolim'}/N2^{int(np.log2(max(N, 2)))}"
+    """Cache key of a single-instance shape.  Up to ONE_LAUNCH_MAX cells it holds N itself: within a bucket
+    there one mesh may run as one launch and the next as one launch per half-step, and a shape tuned on the second
+    would take the first off its one launch (Euler P = 3, N = 300: 3.8 us a half-step, 5.4 to 5.6 in launches)."""
+    size = f"N{N}" if N <= ONE_LAUNCH_MAX else f"N2^{int(np.log2(N))}"
+    return f"single/{equation}/P{P}/{precision}/{'lim' if limiter else 'nolim'}/{size}"
 
 
 # wave-tile shape of each single-instance launch variant: old cells per tile
@@ -120,7 +130,11 @@ def tune_single(solver: "binding.Solver", q0: np.ndarray, cfl: float, steps: int
         return solver.last_run_ms() / steps
 
     default_ms = time_one(default)
-    per_variant = {v: min(r["ms_per_step"] for r in results if r["variant"] == v) for v in variants}
+    # the default shape of a small mesh may be the one-launch form, which is no variant's time
+    own = [r for r in results if solver.N > ONE_LAUNCH_MAX or
+           (r["variant"], r["threads"], r["blocks"]) != (default["variant"], default["threads"], default["blocks"])]
+    per_variant = {v: min(r["ms_per_step"] for r in own if r["variant"] == v)
+                   for v in variants if any(r["variant"] == v for r in own)}
     finalists = [r for r in results if (r["variant"], r["threads"], r["blocks"]) !=
                  (default["variant"], default["threads"], default["blocks"])]
     best = refine(finalists + [{**default, "ms_per_step": default_ms, "is_default": True}], time_one)

@@ -223,8 +223,9 @@ int enqueue_step(wcc_ctx* c, int parity, int slot, double dt_fixed, hipStream_t 
 
 // Whether runs of half-steps go through the one-launch form (wcc_march.hip):
 // meshes of at most march_tiles tiles (where the line is and why: there) in
-// the default launch shape; a shape set by the caller is one of the
-// launch-per-half-step kernels.
+// the default launch shape, also where the caller has set those values (so
+// that a shape read with wcc_get_launch can be set again); any other shape is
+// one of the launch-per-half-step kernels.
 bool marches(const wcc_ctx* c) {
   const int64_t tiles = (std::max(ncells_of(c, 0), ncells_of(c, 1)) + 62) / 63;
   return tiles <= wcc::march_tiles(c->eq, c->P, (int)c->elem) && c->blocks == 0 && c->threads == 256 &&
