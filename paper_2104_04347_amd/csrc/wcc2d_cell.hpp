@@ -340,11 +340,7 @@ __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P +
   }
   const double sum = form(r);
   double inv = wcc::rcp_near(sum);
-  lo = max(lo, wcc::lo_word(sum));
-  // q_m >= eps; a NaN's high word is above every bound
-  bool ok = (wcc::hi_word(eps) - wcc::hi_pow2(-900) < wcc::hi_pow2(0) - wcc::hi_pow2(-900)) &
-            (qh < wcc::hi_pow2(P == 1 ? 900 : 60)) & (lo != 0xffffffffu) & wcc::between_pow2(sum, -900, 900);
-  if (P > 1) ok &= wcc::near_num(st);
+  const bool ok = wcc::near_eps(eps) & wcc::near_weights<P>(qh, lo, sum);
   if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
 #pragma unroll
     for (int m = 0; m < 5; ++m) r[m] = wcc::div_rn_any(st, q[m]);
@@ -379,14 +375,13 @@ __device__ __forceinline__ void gas2(const Phys2& ph, const double (&ab)[4], boo
   g.p = pressure();
   const double gp = ph.gamma * g.p;
   g.c = wcc::sqrt_near(wcc::div_near(gp, rho, y));
-  // the ranges of rho and gamma p put c^2 in [2^-460, 2^400]
-  bool ok = wcc::between_pow2(rho, -300, 60) & wcc::not_ones(rho) & wcc::near_num(ab[1]) & wcc::near_num(ab[2]) &
-            wcc::between_pow2(gp, -400, 100);
+  // the ranges of rho and gamma p put c^2 in [2^-700, 2^700]
+  bool ok = wcc::near_den(rho) & wcc::near_num(ab[1]) & wcc::near_num(ab[2]) & wcc::between_pow2(gp, -400, 400);
   if (CHAR) {
     const double h = ab[3] + g.p;
     g.H = wcc::div_near(h, rho, y);
     g.ic = wcc::rcp_near(g.c);
-    ok &= wcc::between_pow2(h, -400, 100) & wcc::not_ones(g.c);
+    ok &= wcc::between_pow2(h, -400, 400) & wcc::not_ones(g.c);
   }
   if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
     g.u = wcc::div_rn_any(ab[1], rho);
@@ -421,7 +416,7 @@ __device__ __forceinline__ void char_limit2d(const Phys2& ph, double dx, double 
     nx = some ? wcc::div_near(gx, gn, y) : 1.0;
     ny = some ? wcc::div_near(gy, gn, y) : 0.0;
     const bool ok = wcc::near_den(dx) & wcc::near_den(dy) & wcc::near_num(ex) & wcc::near_num(ey) &
-                    ((g2 == 0.0) | (wcc::between_pow2(g2, -300, 100) & wcc::not_ones(gn) & wcc::near_num(gx) &
+                    ((g2 == 0.0) | (wcc::between_pow2(g2, -600, 600) & wcc::not_ones(gn) & wcc::near_num(gx) &
                                     wcc::near_num(gy)));
     if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
       const double hx = wcc::div_rn_any(ex, dx), hy = wcc::div_rn_any(ey, dy);

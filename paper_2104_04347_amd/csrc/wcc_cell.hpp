@@ -297,26 +297,14 @@ __device__ __forceinline__ void limiter_weights(double b0, double b1, double b2,
   double inv;
   if constexpr (NEAR) {
     inv = rcp_near(sum);
-    // The four denominators' ranges.  q_m >= eps >= 2^-900 (near_eps, and
-    // b_m^2 >= 0), so only their upper bound is open, and a NaN's high word
-    // lies above it; sum >= 1 (P = 1: >= 2^-120).  Their low words are
-    // compared together.
-    const uint32_t qh = max(max(hi_word(q0), hi_word(q1)), hi_word(q2));
-    const uint32_t lo = max(max(max(lo_word(q0), lo_word(q1)), lo_word(q2)), lo_word(sum));
-    ok &= (qh < hi_pow2(P == 1 ? 900 : 60)) & (hi_word(sum) < hi_pow2(900)) & (lo != 0xffffffffu);
-    if (P > 1) ok &= near_num(st);
-    if (P == 1) ok &= hi_word(sum) >= hi_pow2(-900);
+    ok &= near_weights<P>(max(max(hi_word(q0), hi_word(q1)), hi_word(q2)),
+                          max(max(lo_word(q0), lo_word(q1)), lo_word(q2)), sum);
   } else {
     inv = div_rn_any(1.0, sum);
   }
   w0 = wh0 * inv;
   w1 = wh1 * inv;
   w2 = wh2 * inv;
-}
-
-// The limiter epsilon allows the near forms at all (a property of the run).
-__device__ __forceinline__ bool near_eps(double eps) {
-  return between_pow2(eps, -900, 0);
 }
 
 // binary32: w_hat = (1 + r0^2, r1^2, r2^2) with r_m = st / q_m (P = 1: with
@@ -408,14 +396,14 @@ __device__ __forceinline__ void euler_uc(const Phys<R>& ph, R rho, R mom, R ene,
     p = ph.gm1 * (ene - 0.5 * mom * u);
     const double gp = ph.gamma * p;
     c = sqrt_near(div_near(gp, rho, y));
-    // the ranges of rho and gamma p put c^2 in [2^-460, 2^400], inside those
+    // the ranges of rho and gamma p put c^2 in [2^-700, 2^700], inside those
     // of the square root and, up to its low word, of 1 / c
-    ok &= between_pow2(rho, -300, 60) & not_ones(rho) & near_num(mom) & between_pow2(gp, -400, 100);
+    ok &= near_den(rho) & near_num(mom) & between_pow2(gp, -400, 400);
     if (CHAR) {
       const double h = ene + p;
       H = div_near(h, rho, y);
       ic = rcp_near(c);
-      ok &= between_pow2(h, -400, 100) & not_ones(c);
+      ok &= between_pow2(h, -400, 400) & not_ones(c);
     }
   } else {
     u = divT(mom, rho);
