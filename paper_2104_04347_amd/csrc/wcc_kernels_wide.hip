@@ -168,7 +168,11 @@ __global__ __launch_bounds__(256) void k_half_step_wide(const StepArgs<R> a) {
   const int t_stop = t_begin + a.per_block < tiles ? t_begin + a.per_block : tiles;
   double dt;
   if (!step_time(ring, a.ctrl, a.parts, a.slot, a.dx, a.dt_fixed, blockIdx.x == 0 && wave == 0, dt)) return;
-  const double lam = div_rn(dt, a.dx);
+  // (The choosing division's join here costs the tile loop up to 22 registers
+  // and with them a wave per SIMD: limited Euler N = 2^20, P = 2 44.6 us a
+  // half-step against 41.5, P = 4 73.7 against 66.7, and on a grid of four blocks
+  // a compute unit 96.6 against 71.9.)
+  const double lam = div_rn_any(dt, a.dx);
   const R nlam = (R)(-lam);
   double smax = 0.0;
   unsigned flags = 0u;

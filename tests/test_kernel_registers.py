@@ -1,0 +1,58 @@
+"""Register use of kernels in the built library (this repository's own build, read from its code objects' metadata):
+those whose time hangs on the waves that fit a SIMD, and those that once spilled."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2104_04347_amd import build
+from test_rounding_isa import BUNDLER, MAGIC, ROCM
+
+READELF = os.path.join(ROCM, "llvm", "bin", "llvm-readelf")
+
+
+def _kernels(lib: str, tmp) -> dict:
+    """Demangled kernel name -> (vector registers, accumulation ones included; spilled vector registers)."""
+    fat, copy = tmp / "fatbin", tmp / "lib.so"
+    shutil.copyfile(lib, copy)                       # objcopy rewrites its input
+    subprocess.run(["objcopy", "--dump-section", f".hip_fatbin={fat}", str(copy), str(tmp / "discard.so")],
+                   check=True, capture_output=True)
+    data = fat.read_bytes()
+    starts = [m.start() for m in re.finditer(re.escape(MAGIC), data)]
+    found = {}
+    for a, b in zip(starts, starts[1:] + [len(data)]):
+        src, co = tmp / "b.bin", tmp / "b.co"
+        src.write_bytes(data[a:b])
+        subprocess.run([BUNDLER, "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
+                        f"--input={src}", f"--output={co}"], check=True, capture_output=True)
+        if co.stat().st_size == 0:
+            continue
+        notes = subprocess.run([READELF, "--notes", str(co)], check=True, capture_output=True, text=True).stdout
+        for kernel in re.split(r"\n  - (?=\.agpr_count)", notes)[1:]:
+            value = lambda key: int(re.search(rf"\.{key}:\s+(\d+)", kernel).group(1))      # noqa: E731
+            found[re.search(r"\.symbol:\s+'?(\S+?)\.kd", kernel).group(1)] = (value("vgpr_count"),
+                                                                               value("vgpr_spill_count"))
+    names = subprocess.run(["c++filt"], input="\n".join(found), capture_output=True, text=True, check=True).stdout
+    return {re.sub(r"^void |\(.*", "", n): v for n, v in zip(names.splitlines(), found.values())}
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    if not (shutil.which("objcopy") and shutil.which("c++filt") and os.path.exists(BUNDLER) and os.path.exists(READELF)):
+        pytest.skip("needs binutils and the ROCm LLVM tools")
+    assert os.path.exists(build.LIB), "build the library first (__graft_entry__.build())"
+    return _kernels(build.LIB, tmp_path_factory.mktemp("co"))
+
+
+def waves_per_simd(registers: int) -> int:
+    """512 registers a SIMD lane, handed out in eights, eight waves at most."""
+    return min(8, 512 // (-(-registers // 8) * 8))
+
+
+# limited Euler in binary64: a wave fewer per SIMD cost up to a quarter of the time at N = 2^20
+@pytest.mark.parametrize("P,waves", [(1, 4), (2, 3), (3, 2), (4, 2)])
+def test_wide_tiles_keep_their_waves(kernels, P, waves):
+    registers, spilled = kernels[f"wcc::k_half_step_wide<2, {P}, true, double>"]
+    assert waves_per_simd(registers) >= waves and spilled == 0, registers
