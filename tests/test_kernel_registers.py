@@ -56,3 +56,10 @@ def waves_per_simd(registers: int) -> int:
 def test_wide_tiles_keep_their_waves(kernels, P, waves):
     registers, spilled = kernels[f"wcc::k_half_step_wide<2, {P}, true, double>"]
     assert waves_per_simd(registers) >= waves and spilled == 0, registers
+
+
+def test_batch_kernels_do_not_spill(kernels):
+    """A bound on the staged degree-1 kernel once made it spill 43 vector registers in binary64 (a fifth of the time)."""
+    batch = {n: v for n, v in kernels.items() if "k_batch_step<" in n}
+    assert len(batch) > 20
+    assert not {n: v for n, v in batch.items() if v[1]}
