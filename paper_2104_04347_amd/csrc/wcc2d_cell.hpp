@@ -323,12 +323,6 @@ __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P +
     for (int k = 1; k <= P; ++k) tau = __builtin_fma(D[k][P - k], D[k][P - k], tau);
     st = sigma * tau;
   }
-  double wh0, wh1, wh2, wh3, wh4;
-  auto form = [&](const double (&r)[5]) {
-    wh0 = P == 1 ? r[0] * r[0] : __builtin_fma(r[0], r[0], 1.0);
-    wh1 = r[1] * r[1]; wh2 = r[2] * r[2]; wh3 = r[3] * r[3]; wh4 = r[4] * r[4];
-    return (((wh0 + wh1) + wh2) + wh3) + wh4;
-  };
   double r[5];
   uint32_t qh = 0u, lo = 0u;
 #pragma unroll
@@ -338,13 +332,28 @@ __device__ __forceinline__ void limit2d(double eps, double abar, double (&D)[P +
     qh = max(qh, wcc::hi_word(q[m]));
     lo = max(lo, wcc::lo_word(q[m]));
   }
-  const double sum = form(r);
+  double wh0 = P == 1 ? r[0] * r[0] : __builtin_fma(r[0], r[0], 1.0);
+  double wh1 = r[1] * r[1], wh2 = r[2] * r[2], wh3 = r[3] * r[3], wh4 = r[4] * r[4];
+  const double sum = (((wh0 + wh1) + wh2) + wh3) + wh4;
   double inv = wcc::rcp_near(sum);
   const bool ok = wcc::near_eps(eps) & wcc::near_weights<P>(qh, lo, sum);
   if (__builtin_expect(__ballot(mine & !ok) != 0, 0)) {
-#pragma unroll
-    for (int m = 0; m < 5; ++m) r[m] = wcc::div_rn_any(st, q[m]);
-    inv = wcc::div_rn_any(1.0, form(r));
+    // One division in the code, six times round: the denominators leave the
+    // ring q as the weights enter it, and the last turn is 1 / sum.  (Six
+    // divisions here, for four fields a cell, compiled in 380 s; this in 108.)
+    double num = st, den = q[0], acc = 0.0;
+#pragma unroll 1
+    for (int m = 0; m < 6; ++m) {
+      inv = wcc::div_rn_any(num, den);
+      const double w = P > 1 && m == 0 ? __builtin_fma(inv, inv, 1.0) : inv * inv;
+      acc = m == 0 ? w : acc + w;
+      num = m < 4 ? st : 1.0;
+      den = m < 4 ? q[1] : acc;
+      if (m < 5) {
+        q[0] = q[1]; q[1] = q[2]; q[2] = q[3]; q[3] = q[4]; q[4] = w;
+      }
+    }
+    wh0 = q[0]; wh1 = q[1]; wh2 = q[2]; wh3 = q[3]; wh4 = q[4];
   }
   const double w0 = wh0 * inv, w1 = wh1 * inv, w2_ = wh2 * inv, w3 = wh3 * inv, w4 = wh4 * inv;
   double dx1 = w0 * D[1][0], dy1 = w0 * D[0][1];

@@ -63,3 +63,23 @@ def test_batch_kernels_do_not_spill(kernels):
     batch = {n: v for n, v in kernels.items() if "k_batch_step<" in n}
     assert len(batch) > 20
     assert not {n: v for n, v in batch.items() if v[1]}
+
+
+def test_2d_limiter_holds_one_general_division_a_field(tmp_path):
+    """The general divisions of the 2D limiter, which data in range never reaches, are one instruction sequence for
+    each characteristic field, run six times.  Six sequences a field took the 2D kernels 380 s to compile, one 108."""
+    from test_rounding_isa import OBJDUMP, _disassemble
+    if not (shutil.which("objcopy") and os.path.exists(BUNDLER) and os.path.exists(OBJDUMP)):
+        pytest.skip("needs objcopy and the ROCm LLVM tools")
+    count, name = {}, None
+    for lines in _disassemble(build.LIB, tmp_path):
+        for line in lines:
+            m = re.match(r"^[0-9a-f]+ <(\S+)>:", line)
+            if m:
+                name = m.group(1)
+            elif "v_div_fixup_f64" in line:
+                count[name] = count.get(name, 0) + 1
+    rows = {n: c for n, c in count.items() if "k2d_half_step_rowsILi2ELi3ELb1E" in n}
+    assert rows
+    # 4 fields; the gas state 6, the gradient's direction 4; 1 / rho of the old cell; dt and the two ratios dt / dx
+    assert max(rows.values()) <= 4 + 6 + 4 + 1 + 3, rows
