@@ -2,10 +2,11 @@
  *
  * Diagnostic library only: libwcc_timeline.so exports the whole C ABI of
  * wcc.h and wcc2d.h, built from the same kernel sources, plus the calls
- * below; its half-step kernels also record, for every wave, the constant
- * 100 MHz clock and the shader clock counter at entry and exit and the
- * hardware placement (HW_ID and XCC_ID registers).  The product library
- * libwcc.so does not contain them.  The records answer what the kernel trace
+ * below.  Every half-step is a launch of its own there, also on the small
+ * meshes for which libwcc.so takes many in one.  Its half-step kernels record,
+ * for every wave, the constant 100 MHz clock and the shader clock counter at
+ * entry and exit and the hardware placement (HW_ID and XCC_ID registers).  The
+ * product library libwcc.so contains neither.  The records answer what the kernel trace
  * cannot: how long each wave lives, how many waves share a SIMD over the
  * launch, and the shader clock the waves ran at (the ratio of the two clocks),
  * against which an instruction-issue roof is priced.

@@ -7,7 +7,8 @@ linked into one shared library that exports the C ABI of include/wcc.h.
 
 The same build links the diagnostic library libwcc_timeline.so: the product
 objects with the three kernel translation units replaced by their timestamped
-builds (csrc/wcc_timeline_*.hip, which include the kernel sources unchanged).
+builds (csrc/wcc_timeline_*.hip, which include the kernel sources unchanged) and
+the one-launch form of small meshes left out.
 Only paper_2104_04347_amd/timeline.py loads it.
 """
 from __future__ import annotations
@@ -28,7 +29,7 @@ ROOT = os.path.dirname(HERE)
 SOURCES = ["wcc_kernels.hip", "wcc_kernels_wide.hip", "wcc_march.hip", "wcc_ctrl.hip", "wcc_host.hip", "wcc_batch.hip", "wcc_api.hip", "wcc2d_kernels.hip", "wcc2d_api.hip"]
 # diagnostic build: kernel translation unit -> its timestamped replacement
 TIMELINE_SOURCES = {"wcc_kernels.hip": "wcc_timeline_1d.hip", "wcc_kernels_wide.hip": "wcc_timeline_1d_wide.hip",
-                    "wcc2d_kernels.hip": "wcc_timeline_2d.hip"}
+                    "wcc2d_kernels.hip": "wcc_timeline_2d.hip", "wcc_march.hip": "wcc_timeline_march.hip"}
 ARCH = "gfx950"
 
 HIPFLAGS = [

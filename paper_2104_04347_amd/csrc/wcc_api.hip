@@ -229,7 +229,7 @@ int enqueue_step(wcc_ctx* c, int parity, int slot, double dt_fixed, hipStream_t 
 bool marches(const wcc_ctx* c) {
   const int64_t tiles = (std::max(ncells_of(c, 0), ncells_of(c, 1)) + 62) / 63;
   return tiles <= wcc::march_tiles(c->eq, c->P, (int)c->elem) && c->blocks == 0 && c->threads == 256 &&
-         c->prefetch == c->default_variant;
+         c->prefetch == c->default_variant && wcc::march_built();
 }
 
 template <class R>

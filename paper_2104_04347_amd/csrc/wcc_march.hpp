@@ -41,6 +41,10 @@ constexpr int march_tiles(int eq, int P, int elem_bytes) {
   return eq != kEuler || P <= 1 ? 16 : (P == 2 || elem_bytes == 4 ? 12 : 8);
 }
 
+// Whether this library holds the kernels of this form (the diagnostic one, which
+// records launches, does not).
+bool march_built();
+
 template <class R>
 hipError_t launch_march(const MarchArgs<R>& a, int eq, int P, bool lim, hipStream_t s);
 
