@@ -301,7 +301,8 @@ int wcc_batch_read_dofs(wcc_batch* bt, int b, double* host, int64_t cap, wcc_sta
  * stored in whole 64-cell groups; 5 and 6 = grouped with direct / staged
  * stores, the degrees' launches captured as parallel branches of the run's
  * graphs so that they may overlap on the device; other values return
- * WCC_EINVAL).  Until this is called: 5 in binary64, 6 FP32-mixed. */
+ * WCC_EINVAL).  Until this is called: 5, or 6 for an FP32-mixed batch whose two
+ * state buffers exceed 512 MiB. */
 int wcc_batch_set_schedule(wcc_batch* bt, int threads_per_block, int blocks, int mode);
 /* Device time of the last wcc_batch_advance call, in ms (waits for it). */
 int wcc_batch_last_run_ms(wcc_batch* bt, double* ms);

@@ -307,7 +307,7 @@ struct wcc_batch {
   int64_t p_total = 0, d_total = 0;      // elements per buffer
   // schedule
   bool grouped = true;
-  bool staged = false;                   // line-aligned stores through LDS (default: FP32-mixed, see wcc_batch_create)
+  bool staged = false;                   // line-aligned stores through LDS (default: see wcc_batch_create)
   bool branches = true;                  // grouped: the degrees' launches as parallel graph branches
   int threads = 256, blocks = 0, cu = 256;
   std::vector<int64_t> block_start;      // fused: blocks+1 entries; grouped: per group blocks+1 entries, concatenated
@@ -581,11 +581,6 @@ int wcc_batch_create(int equation, int B, const int32_t* P, const int64_t* N, in
   b->B = B;
   b->prm = prm;
   b->elem = prm.precision == WCC_FP64 ? 8 : 4;
-  // Parallel degree branches, with staged stores in the FP32-mixed mode: 512
-  // instances (7M cells) 155 against 165 us a half-step, 64 (0.7M) 26 against
-  // 33, 16 (40k) alike.  In binary64 the staging area leaves too few waves:
-  // 310 against 236 and 39 against 35.
-  b->staged = prm.precision != WCC_FP64;
   b->inst.resize(B);
   for (int i = 0; i < B; ++i) {
     BatchInst& in = b->inst[i];
@@ -600,6 +595,18 @@ int wcc_batch_create(int equation, int B, const int32_t* P, const int64_t* N, in
     b->p_total += (int64_t)b->nc * in.ld;
     b->d_total += (int64_t)b->nc * P[i] * in.ld;
   }
+  // Default stores, the degrees' launches as parallel branches: staged where an
+  // FP32-mixed state outgrows the 256 MB Infinity Cache by a factor two, as for
+  // one instance (wcc_create); below, partial lines cost nothing and the
+  // block-wide barriers do.  us a half-step, direct and staged, mixed degrees:
+  //   FP32-mixed   3 MiB 12.7 13.3;   35 MiB (run of 24) 18.5 19.3;
+  //              176 MiB 46.0 47.2;  333 MiB 86.5 90.0;  447 MiB 114.3 119.2;
+  //              637 MiB 164.9 159.2; 1,021 MiB 268.2 245.1
+  //              (73 MiB in 150 short instances, the exception: 30.6 27.0)
+  //   binary64   265 MiB 71.3 80.8;  960 MiB 248.1 282.0: never, the staging
+  //              area leaves too few waves
+  const double state_bytes = 2.0 * (8.0 * (double)b->p_total + (double)b->elem * (double)b->d_total);
+  b->staged = prm.precision != WCC_FP64 && state_bytes > 512.0 * 1048576.0;
   // tiles grouped by degree, instances in input order inside a group
   for (int p = 0; p <= wcc::kBatchPMax; ++p) {
     b->group_begin[p] = (int64_t)b->tiles.size();
