@@ -368,8 +368,8 @@ __global__ __launch_bounds__(256) void k2d_half_step_rows(const Step2Args a) {
   // had not issued ahead, and the loop's code was half as long again.  The row
   // kernels are bound by issue and by the latency of dependent binary64 chains
   // at one wave per SIMD (Euler).  With the near divisions of the limiter, us a
-  // half-step before and after: Burgers 1024 x 1024 41.9 and 38.9, unlimited
-  // Euler 768 x 768 104.9 and 102.2, limited Euler 600 x 600 78.5 and 71.2
+  // half-step before and after: Burgers 1024 x 1024 41.7 and 38.5, unlimited
+  // Euler 768 x 768 104.5 and 101.9, limited Euler 600 x 600 78.3 and 70.5
   // (P = 3).
   bool prime = true;
   while (left > 0) {

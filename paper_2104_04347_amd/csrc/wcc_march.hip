@@ -12,9 +12,11 @@
 // memory is read at the start and written at the end, as that many launches
 // would leave it.
 //
-// What bounds it: the dependent binary64 chains of one cell (about 900
-// instructions for Euler, P = 3, 6 cycles each with one wave per SIMD), then
-// the compute unit's issue rate (march_tiles in wcc_march.hpp).
+// What bounds it: the dependent binary64 chains of one cell, then the compute
+// unit's issue rate.  Counters (Euler, P = 3, 915 vector instructions a wave and
+// half-step): with one wave per SIMD 2.5 us, vector issue 0.65 of the time; with
+// two 3.9 us, 0.82; P = 1 with four 4.3 us, 0.94.  Advection P = 2, one wave:
+// 1.0 us, 0.48.  (march_tiles in wcc_march.hpp.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

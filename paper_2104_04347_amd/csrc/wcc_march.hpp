@@ -24,17 +24,22 @@ struct MarchArgs {
   unsigned long long* parts;
 };
 
-// Half-steps one launch may take: about 10 ms at the largest mesh.
+// Half-steps one launch may take: 16 to 20 ms at the largest meshes, 4 ms at one
+// tile of a scalar equation.
 constexpr int kMarchSteps = 4096;
 
 // Wave tiles (one wave each) that one work-group marches.  The state of that
 // many tiles, twice, fits its 160 KB of LDS, and up to there a half-step is
 // faster than as a launch of its own (us, binary64 unless noted, march
-// against launches, full work-group):
-//   Euler   P = 1: 16 tiles 4.21 / 4.40;  P = 2: 12 tiles 4.41 / 5.06;
-//           P = 3: 8 tiles 3.96 / 5.67 (one wave per SIMD: 2.54 / 5.41);
-//           P = 4: 8 tiles 4.92 / 6.55;  FP32-mixed P = 3, 12 tiles 4.20 / 5.00
-//   scalar  16 tiles: Burgers P = 1 1.83 / 3.74, P = 4 3.15 / 4.18
+// against launches of the default shape, full work-group):
+//   Euler   P = 0: 16 tiles 1.96 / 3.69;  P = 1: 16 tiles 4.30 / 4.39;
+//           P = 2: 12 tiles 4.41 / 4.97;
+//           P = 3: 8 tiles 3.91 / 5.51 (one wave per SIMD: 2.49 / 5.18);
+//           P = 4: 8 tiles 4.85 / 6.25
+//           FP32-mixed P = 1: 16 tiles 3.22 / 4.05;  P = 2, 3, 4: 12 tiles
+//           3.20 / 4.46, 3.99 / 4.94, 5.05 / 5.59
+//   scalar  16 tiles: Burgers P = 1 1.81 / 3.64, P = 3 2.58 / 3.84,
+//           P = 4 3.11 / 4.06; advection P = 4 2.67 / 3.98
 // With four waves of the higher degrees on a SIMD the one compute unit's issue
 // rate costs what the launches did.
 constexpr int march_tiles(int eq, int P, int elem_bytes) {
